@@ -43,21 +43,22 @@ def tet_stage_bytes(N: int, bits: int, reads_res: bool) -> int:
     return 4 * NP * ts * (3 + int(reads_res)) + 32 * ts + 8 * 4
 
 
-def stage_bytes(N: int, bits: int, reads_res: bool) -> int:
+def stage_bytes(N: int, bits: int, reads_res: bool, node: bool = False) -> int:
     """Algorithmic HBM bytes of one stage for one wedge.
 
     State U read and U' written, residual written (and read after the first
     stage): 4 fields x Np values each; per-element geometry and material
     record (40 values), triangular operator (N <= 3: none, the stage factors
-    M^{tri,k} from the record's vertex weights; N >= 4: L^{tri,k}, Np_tri^2
-    values padded to a multiple of 4) and connectivity (8 int32).  Neighbour
+    M^{tri,k} from the record's vertex weights; N >= 4: the lower triangle of
+    its inverse, or on the node-lane kernel L^{tri,k} whole, padded to a
+    multiple of 4 values) and connectivity (8 int32).  Neighbour
     traces are counted as cache hits.  At N = 3 in FP32 this is 2752 B (2112 B
     in the first stage).
     """
     NT = (N + 1) * (N + 2) // 2
     NP = NT * (N + 1)
     ts = bits // 8
-    LS = 0 if N <= 3 else (NT * NT + 3) // 4 * 4
+    LS = 0 if N <= 3 else ((NT * NT if node else NT * (NT + 1) // 2) + 3) // 4 * 4
     state = 4 * NP * ts
     return state * (3 + int(reads_res)) + 40 * ts + LS * ts + 8 * 4
 
@@ -514,8 +515,8 @@ def forward_leg(config: str, bits: int, steps: int, warmup: int, layer_march: st
     kernels = {}
     if Kw:
         avg = w_ms * 1e3 / nlaunch
-        rec_bytes = Kw * (stage_bytes(N, bits, False) + 4 * stage_bytes(N, bits, True)) / 5
-        node = N >= 4 and bits == 32 and wedge_kernel in ("node", "auto")
+        node = N >= 4 and bits == 32 and (wedge_kernel == "node" or (wedge_kernel == "auto" and Kw < 32))
+        rec_bytes = Kw * (stage_bytes(N, bits, False, node) + 4 * stage_bytes(N, bits, True, node)) / 5
         kernels["wedge_stage"] = {"avg_us": avg, "variant": "node-lane" if node else "level-lane",
                                   "bytes_per_launch": Kw * table_stage_bytes(N, bits),
                                   "GBs": Kw * table_stage_bytes(N, bits) / avg / 1e3,
@@ -693,11 +694,11 @@ def main():
     if default_run and not args.no_legs:
         legs = {}
         for name, cfg, b, tk, wk in (("cfg3", "cfg3", 32, "mfma", "auto"), ("cfg3_tet_valu", "cfg3", 32, "valu", "auto"),
-                                     ("cfg3_wedge_level", "cfg3", 32, "mfma", "level"),
+                                     ("cfg3_wedge_node", "cfg3", 32, "mfma", "node"),
                                      ("cfg5_forward", "cfg5", 32, "mfma", "auto"), ("order4", "order4", 32, "mfma", "auto"),
-                                     ("order4_wedge_level", "order4", 32, "mfma", "level"),
+                                     ("order4_wedge_node", "order4", 32, "mfma", "node"),
                                      ("order5", "order5", 32, "mfma", "auto"),
-                                     ("order5_wedge_level", "order5", 32, "mfma", "level"),
+                                     ("order5_wedge_node", "order5", 32, "mfma", "node"),
                                      ("cfg2_fp64", "cfg2", 64, "mfma", "auto")):
             legs[name], _, _ = forward_leg(cfg, b, args.leg_steps, 10, tet_kernel=tk, wedge_kernel=wk)
         # layer marching (the paper's future work) against the gathers, same kernel

@@ -156,11 +156,12 @@ int wdg_set_tet_kernel(wdg_ctx* ctx, int variant);
 
 /* Which wedge stage kernel runs (both compute the stage of Sec. 4.2-4.3 up to
  * rounding order).  The level-lane kernel gives each lane one GLL level of an
- * element (the level's triangular slice of the four equations); the
- * node-lane kernel, which exists for orders 4 and 5 in FP32, gives each lane
+ * element (the level's triangular slice of one equation, a wavefront per
+ * equation); the node-lane kernel, which exists for orders 4 and 5 in FP32, gives each lane
  * one triangle node (the node's vertical line of GLL levels).  Layer
  * marching and the adjoint sweep always use the level-lane kernel.
- * WDG_WEDGE_AUTO (default): node-lane wherever it exists, else level-lane.
+ * WDG_WEDGE_AUTO (default): level-lane, but for meshes of fewer than 32
+ * wedges node-lane wherever it exists.
  * WDG_WEDGE_LEVEL: level-lane everywhere.  WDG_WEDGE_NODE: node-lane
  * wherever it exists.  Other values: WDG_ERR_ARG. */
 enum { WDG_WEDGE_AUTO = 0, WDG_WEDGE_LEVEL = 1, WDG_WEDGE_NODE = 2 };
@@ -308,15 +309,14 @@ int wdg_set_adjoint_memory_limit(wdg_ctx* ctx, int64_t bytes);
  *     meshes of wedges only (else WDG_ERR_UNSUPPORTED); the batch keeps the
  *     pointer (the caller keeps ownership and must not destroy or step the
  *     context while a batch call runs).  index (may be NULL) receives its slot.
- *   wdg_batch_prepare: groups the problems by order and lists their element
- *     chunks problem by problem (one block per chunk, each XCD a contiguous
- *     range); with autotune != 0 (the tuning of elements per block of
- *     Sec. 6.3) times, for every order, the shapes of the stage kernel that
- *     order's problems use alone (wdg_set_wedge_kernel; the node-lane kernel
- *     only if all of them use it) -- the node-lane kernel at four element
- *     counts per block, or the level-lane kernel compiled for 2 waves per
- *     SIMD (as the single-problem kernel) and for 1 (twice the registers) --
- *     on the real data, as the median of five
+ *   wdg_batch_prepare: groups the problems by order and by the stage kernel
+ *     they use alone (wdg_set_wedge_kernel) and lists their element chunks
+ *     problem by problem (one block per chunk, each XCD a contiguous range);
+ *     with autotune != 0 (the tuning of elements per block of Sec. 6.3) times,
+ *     for every group, the shapes of its kernel -- the node-lane kernel at four
+ *     element counts per block, or the level-lane kernel compiled for as many
+ *     waves per SIMD as the single-problem kernel and for one fewer (more
+ *     registers) -- on the real data, as the median of five
  *     launches that rewrite only the residual (which the next stage
  *     overwrites anyway), and keeps the fastest; without autotuning the first
  *     candidate (the single-problem kernel's shape).  Then it captures the
@@ -327,7 +327,8 @@ int wdg_set_adjoint_memory_limit(wdg_ctx* ctx, int64_t bytes);
  *     not recorded by batch steps, and a forward recording (wdg_adjoint_record)
  *     of a problem ends.
  *   wdg_batch_config: elements per block, the chosen waves per SIMD of order N
- *     and the tuned median stage time of that order (microseconds).
+ *     and the tuned median stage time of that order (microseconds); of an
+ *     order with problems on both kernels, the level-lane group's.
  *   wdg_batch_trials: the autotuner's candidates for order N in the order
  *     tried: kernel (WDG_WEDGE_LEVEL or WDG_WEDGE_NODE), elements per block,
  *     waves per SIMD and median stage time (microseconds); up to cap of them

@@ -99,7 +99,8 @@ struct wdg_ctx {
   bool own_state = true;
   int cur = 0;
   void* dGeo = nullptr;
-  void* dL = nullptr;
+  void* dL = nullptr;   // (M^{tri,k})^-1, packed
+  void* dLn = nullptr;  // node-lane kernel (orders 4, 5 in FP32): L^{tri,k}
   void* dSrcVec = nullptr;
   double* dAux = nullptr;
   double* dMv = nullptr;
@@ -194,6 +195,7 @@ void release_device(wdg_ctx* ctx) {
   ctx->own_state = true;
   dfree(ctx->dGeo);
   dfree(ctx->dL);
+  dfree(ctx->dLn);
   dfree(ctx->dAdjCp);
   dfree(ctx->dAdjStore);
   ctx->adj_store_bytes = 0;
@@ -414,15 +416,28 @@ int upload_sources(wdg_ctx* ctx) {
   return WDG_OK;
 }
 
-// one Runge-Kutta stage (or, with a = 0, dt = 1, no U write, a plain RHS)
 // Whether the wedges of a stage with these flags run on the node-lane kernel:
 // it exists for orders 4 and 5 in FP32, without layer marching and outside
-// the adjoint sweep (which only the level-lane kernel implements); by default
-// it is the default wherever it exists (measured faster at orders 4 and 5:
-// 122 against 137 us and 209 against 309 us per stage on 73 728 wedges).
+// the adjoint sweep (which only the level-lane kernel implements).  By default
+// only meshes of a block or two run on it: there a stage is one block's
+// latency either way (24 wedges: 10.1 us against 8.4 level-lane at order 4),
+// and a batch of such problems keeps its search over block shapes.  From 32
+// wedges on the level-lane kernel with a wavefront per equation is the default
+// (us per stage, level-lane against node-lane: order 4 8.8 / 10.4 on 128
+// wedges, 28 / 32 on 18 432, 86 / 106 on 73 728; order 5 11.9 / 14.3,
+// 49 / 53, 156 / 193).
+constexpr int64_t kNodeAutoWedges = 32;
 bool node_kernel(const wdg_ctx* ctx, int flags) {
   if (ctx->N < 4 || ctx->bits != 32 || (flags & (wdg::kLayerMarch | wdg::kGrad))) return false;
-  return ctx->wedge_kernel == WDG_WEDGE_NODE || ctx->wedge_kernel == WDG_WEDGE_AUTO;
+  return ctx->wedge_kernel == WDG_WEDGE_NODE || (ctx->wedge_kernel == WDG_WEDGE_AUTO && ctx->Kw < kNodeAutoWedges);
+}
+
+// Cache policy of a stage: the residual and the output state stream past the caches.
+int stream_flags(size_t, size_t) { return wdg::kStreamRes | wdg::kStreamU; }
+size_t state_bytes(const wdg_ctx* ctx) { return size_t(ctx->nodes()) * 4 * ctx->tsize(); }
+size_t record_bytes(const wdg_ctx* ctx) {
+  return size_t(ctx->Kw) * (wdg::kGeoStride * ctx->tsize() + wdg::kConnStride * sizeof(int)) +
+         size_t(ctx->Kt) * (wdg::kTetGeoStride * ctx->tsize() + wdg::kTetConnStride * sizeof(int));
 }
 
 hipError_t launch_wedges(const wdg_ctx* ctx, const wdg::StageLaunch& L) {
@@ -433,6 +448,7 @@ hipError_t launch_wedges(const wdg_ctx* ctx, const wdg::StageLaunch& L) {
   return wdg::launch_wedge_stage(ctx->N, ctx->bits, L, ctx->stream);
 }
 
+// one Runge-Kutta stage (or, with a = 0, dt = 1, no U write, a plain RHS)
 int launch_stage(wdg_ctx* ctx, const void* Uin, void* Uout, void* res, double a, double b, double dt, double tstage,
                  int flags, double g = 1.0, void* rout = nullptr, bool sources = true, const void* gUs = nullptr,
                  const void* gRs = nullptr, void* gacc = nullptr, double gb = 0.0) {
@@ -442,6 +458,7 @@ int launch_stage(wdg_ctx* ctx, const void* Uin, void* Uout, void* res, double a,
   L.res = res;
   L.geo = ctx->dGeo;
   L.L = ctx->dL;
+  L.Ln = ctx->dLn;
   L.conn = ctx->dConn;
   L.geoT = ctx->dGeoT;
   L.connT = ctx->dConnT;
@@ -474,7 +491,10 @@ int launch_stage(wdg_ctx* ctx, const void* Uin, void* Uout, void* res, double a,
   L.tet_blocks = ctx->tet_blocks;
   L.cols = ctx->dCols;
   L.ncols = ctx->ncols;
-  L.flags = flags | (g != 1.0 ? wdg::kGamma : 0) | (ctx->layer_march != WDG_MARCH_OFF ? wdg::kLayerMarch : 0) |
+  // (the adjoint's forward and reverse stages walk through many states)
+  const int stream = (flags & (wdg::kResOut | wdg::kGrad)) ? wdg::kStreamRes | wdg::kStreamU
+                                                           : stream_flags(state_bytes(ctx), record_bytes(ctx));
+  L.flags = flags | stream | (g != 1.0 ? wdg::kGamma : 0) | (ctx->layer_march != WDG_MARCH_OFF ? wdg::kLayerMarch : 0) |
             (ctx->layer_march == WDG_MARCH_COLUMN ? wdg::kColumnMarch : 0) | (ctx->tet_valu ? wdg::kTetValu : 0) | (ctx->bc == WDG_BC_DIRICHLET_P0 ? wdg::kDirichlet : 0) |
             (ctx->flux == WDG_FLUX_CENTRAL ? wdg::kCentral : 0) | (ctx->mass == WDG_MASS_LUMPED ? wdg::kLumped : 0);
   if (ctx->timing) {
@@ -1102,6 +1122,7 @@ int wdg_set_mesh(wdg_ctx* ctx, int64_t nv, const double* vxyz, int64_t nw, const
   HIPCHK(hipMalloc(&ctx->dRes, nstate));
   HIPCHK(hipMalloc(&ctx->dGeo, kw1 * wdg::kGeoStride * ts));
   HIPCHK(hipMalloc(&ctx->dL, kw1 * LS * ts));
+  if (ctx->N >= 4 && ctx->bits == 32) HIPCHK(hipMalloc(&ctx->dLn, kw1 * wdg::node_lift_stride(ctx->N) * ts));
   HIPCHK(hipMalloc(&ctx->dAux, kw1 * wdg::kAuxStride * sizeof(double)));
   HIPCHK(hipMalloc(&ctx->dConn, kw1 * wdg::kConnStride * sizeof(int32_t)));
   HIPCHK(hipMalloc(&ctx->dMv, 3 * size_t(R.NT) * R.NT * sizeof(double)));
@@ -1128,7 +1149,8 @@ int wdg_set_mesh(wdg_ctx* ctx, int64_t nv, const double* vxyz, int64_t nw, const
     HIPCHK(hipMemcpyAsync(dMtri, R.Mtri.data(), R.Mtri.size() * sizeof(double), hipMemcpyHostToDevice, ctx->stream));
     HIPCHK(hipMemcpyAsync(ctx->dConn, ctx->conn.data(), ctx->conn.size() * sizeof(int32_t), hipMemcpyHostToDevice,
                           ctx->stream));
-    HIPCHK(wdg::launch_setup(ctx->N, ctx->bits, Kw, dX, ctx->dMv, dMtri, ctx->dGeo, ctx->dL, ctx->dAux, ctx->stream));
+    HIPCHK(wdg::launch_setup(ctx->N, ctx->bits, Kw, dX, ctx->dMv, dMtri, ctx->dGeo, ctx->dL, ctx->dLn, ctx->dAux,
+                             ctx->stream));
     HIPCHK(hipStreamSynchronize(ctx->stream));
     HIPCHK(hipFree(dX));
     HIPCHK(hipFree(dMtri));
@@ -2145,7 +2167,6 @@ int wdg_get_element_data(const wdg_ctx* ctx, double* geo, double* lift) {
   if (ctx->host_only || ctx->state < kMesh) return fail(ctx, WDG_ERR_STATE, "no device mesh");
   HIPCHK(hipSetDevice(ctx->device));
   const int NT = ctx->NT();
-  const int LS = wdg::lift_stride(ctx->N);
   auto fetch = [&](const void* src, size_t count, double* dst, int stride, int used) -> int {
     std::vector<unsigned char> buf(count * ctx->tsize());
     HIPCHK(hipMemcpyAsync(buf.data(), src, buf.size(), hipMemcpyDeviceToHost, ctx->stream));
@@ -2162,10 +2183,11 @@ int wdg_get_element_data(const wdg_ctx* ctx, double* geo, double* lift) {
     int rc = fetch(ctx->dGeo, size_t(ctx->Kw) * wdg::kGeoStride, geo, wdg::kGeoStride, wdg::kGeoStride);
     if (rc) return rc;
   }
-  if (lift && !wdg::lift_packed(ctx->N)) {
+  if (lift && ctx->dLn) {
     // the record holds L^{tri,k} column by column
     std::vector<double> cm(size_t(ctx->Kw) * NT * NT);
-    int rc = fetch(ctx->dL, size_t(ctx->Kw) * LS, cm.data(), LS, NT * NT);
+    const int LS = wdg::node_lift_stride(ctx->N);
+    int rc = fetch(ctx->dLn, size_t(ctx->Kw) * LS, cm.data(), LS, NT * NT);
     if (rc) return rc;
     for (int64_t k = 0; k < ctx->Kw; ++k)
       for (int r = 0; r < NT; ++r)
@@ -2174,6 +2196,7 @@ int wdg_get_element_data(const wdg_ctx* ctx, double* geo, double* lift) {
     // L^{tri,k} = (M^{tri,k})^-1 M^tri from the stored lower triangle of the inverse
     const int NPK = NT * (NT + 1) / 2;
     std::vector<double> pk(size_t(ctx->Kw) * NPK);
+    const int LS = wdg::lift_stride(ctx->N);
     int rc = fetch(ctx->dL, size_t(ctx->Kw) * LS, pk.data(), LS, NPK);
     if (rc) return rc;
     const RefOps& R = *ctx->ref;
@@ -2261,7 +2284,7 @@ struct wdg_batch {
   struct Group {
     int N = 0;
     std::vector<int> members;  // problem indices
-    bool node = false;         // node-lane kernel (orders 4, 5 in FP32), else level-lane
+    bool node = false;         // node-lane kernel (node_kernel), else level-lane
     int epb = 0, wpe = 2, nwork = 0;
     int2* dWork = nullptr;
     float tuned_us = 0.0f;
@@ -2332,6 +2355,11 @@ int batch_upload_records(wdg_batch* b) {
   const size_t np = b->probs.size();
   std::vector<wdg::StageLaunch> L(np);
   std::vector<wdg::BatchParam> P(np);
+  size_t sb = 0, rb = 0;  // of all problems: a stage walks through every one
+  for (const wdg_ctx* q : b->probs) {
+    sb += state_bytes(q);
+    rb += record_bytes(q);
+  }
   for (size_t i = 0; i < np; ++i) {
     wdg_ctx* ctx = b->probs[i];
     wdg::StageLaunch& A = L[i];
@@ -2341,6 +2369,7 @@ int batch_upload_records(wdg_batch* b) {
     A.res = ctx->dRes;
     A.geo = ctx->dGeo;
     A.L = ctx->dL;
+    A.Ln = ctx->dLn;
     A.conn = ctx->dConn;
     A.opsW = ctx->dOpsW;
     A.srcvec = ctx->dSrcVec;
@@ -2351,7 +2380,8 @@ int batch_upload_records(wdg_batch* b) {
     A.Kw = ctx->Kw;
     const int flags = (ctx->bc == WDG_BC_DIRICHLET_P0 ? wdg::kDirichlet : 0) |
                       (ctx->flux == WDG_FLUX_CENTRAL ? wdg::kCentral : 0) |
-                      (ctx->mass == WDG_MASS_LUMPED ? wdg::kLumped : 0);
+                      (ctx->mass == WDG_MASS_LUMPED ? wdg::kLumped : 0) |
+                      stream_flags(sb, rb);
     A.flags = flags;  // a stage-1 launch without U write: the state of the autotuning runs
     wdg::BatchParam& Q = P[i];
     Q = wdg::BatchParam{};
@@ -2436,17 +2466,24 @@ int wdg_batch_prepare(wdg_batch* b, int autotune) {
   batch_release(b);
   b->groups.clear();
   for (size_t i = 0; i < b->probs.size(); ++i) {
+    // one group per order and kernel family: each problem runs on the family
+    // it uses alone, so that batch results equal its own bit for bit
     const int N = b->probs[i]->N;
-    auto it = std::find_if(b->groups.begin(), b->groups.end(), [N](const wdg_batch::Group& g) { return g.N == N; });
+    const bool node = node_kernel(b->probs[i], 0);
+    auto it = std::find_if(b->groups.begin(), b->groups.end(),
+                           [N, node](const wdg_batch::Group& g) { return g.N == N && g.node == node; });
     if (it == b->groups.end()) {
       b->groups.emplace_back();
       b->groups.back().N = N;
+      b->groups.back().node = node;
       it = b->groups.end() - 1;
     }
     it->members.push_back(int(i));
   }
   std::sort(b->groups.begin(), b->groups.end(),
-            [](const wdg_batch::Group& x, const wdg_batch::Group& y) { return x.N > y.N; });
+            [](const wdg_batch::Group& x, const wdg_batch::Group& y) {
+              return x.N != y.N ? x.N > y.N : x.node < y.node;
+            });
   const size_t np = b->probs.size();
   BHIPCHK(hipMalloc(&b->dProbs, np * sizeof(wdg::StageLaunch)));
   BHIPCHK(hipMalloc(&b->dParam, np * sizeof(wdg::BatchParam)));
@@ -2457,8 +2494,8 @@ int wdg_batch_prepare(wdg_batch* b, int autotune) {
   // autotuner (the paper tunes its elements per block, Sec. 6.3): per order,
   // the kernel shapes that exist for it -- the node-lane kernel (orders 4, 5
   // in FP32) at kNodeEpbVariants element counts per block, the level-lane
-  // kernel at its register budgets (occupancy 2 as the single-problem kernel,
-  // or 1: no spills at high order) -- each timed on the real data as the
+  // kernel at two register budgets (the single-problem kernel's wavefronts
+  // per SIMD, and one fewer) -- each timed on the real data as the
   // median of kTuneReps launches that only rewrite the residual (harmless at
   // a step boundary, where the next stage overwrites it before reading)
   constexpr int kTuneReps = 5;
@@ -2471,17 +2508,13 @@ int wdg_batch_prepare(wdg_batch* b, int autotune) {
       bool node;
       int epb, wpe;
     };
-    // the kernel family the problems of this order use alone (so that batch
-    // results equal theirs bit for bit): node-lane only if every one does;
     // first the single-problem kernel's shape (the choice without autotuning)
-    bool node = true;
-    for (int p : g.members) node = node && node_kernel(b->probs[p], 0);
     std::vector<Cand> cand;
-    if (node) {
+    if (g.node) {
       for (int k = 0; k < wdg::kNodeEpbVariants; ++k) cand.push_back({true, wdg::wedge_node_epb(g.N, b->bits, k), 2});
     } else {
-      cand.push_back({false, wdg::wedge_chunk_elems(g.N, b->bits), 2});
-      cand.push_back({false, wdg::wedge_chunk_elems(g.N, b->bits), 1});
+      for (int k = 0; k < 2; ++k)
+        cand.push_back({false, wdg::wedge_chunk_elems(g.N, b->bits), wdg::wedge_waves(g.N, b->bits, k)});
     }
     g.trials.clear();
     size_t pick = 0;

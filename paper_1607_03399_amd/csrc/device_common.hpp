@@ -18,15 +18,10 @@ struct Dim {
   static constexpr int NT = (N + 1) * (N + 2) / 2;
   static constexpr int Nq = N + 1;
   static constexpr int NP = NT * Nq;
-  // Per-element triangular operator: for N <= 3 (M^{tri,k})^-1, stored as its
-  // lower triangle row by row (symmetric; the stage kernel does not read it:
-  // it factors M^{tri,k} itself into the same LDS slots and solves after the
-  // literal M^tri); for N >= 4 the lift L^{tri,k} = (M^{tri,k})^-1 M^tri
-  // itself, column by column (the node-lane kernel reads a row per lane,
-  // coalesced across the element's lanes).  Padded to whole 4-vectors.
-  static constexpr bool PACKED = N <= 3;
+  // Per-element triangular operator (M^{tri,k})^-1, stored as its lower
+  // triangle row by row (symmetric), padded to whole 4-vectors.
   static constexpr int NPK = NT * (NT + 1) / 2;
-  static constexpr int LS = ((PACKED ? NPK : NT * NT) + 3) / 4 * 4;
+  static constexpr int LS = (NPK + 3) / 4 * 4;
 };
 
 // row of entry f of a lower triangle stored row by row (entry (r, c) at r (r + 1) / 2 + c)
@@ -100,31 +95,33 @@ constexpr int kRsrcWord3 = 0x00020000;
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t chunk_rsrc(const void* base, int64_t bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, int(bytes), kRsrcWord3);
 }
-template <typename T>
+// Cache policy of the stage outputs' stores and of loads that nothing else
+// reads, where the next stage reads the outputs back from HBM anyway:
+// streaming (non-temporal).
+constexpr int kStream = 2;
+template <typename T, int AUX = 0>
 __device__ __forceinline__ V4<T> bload(__amdgpu_buffer_rsrc_t r, int idx) {
   if constexpr (sizeof(T) == 4) {
-    return __builtin_bit_cast(V4<T>, __builtin_amdgcn_raw_buffer_load_b128(r, idx * 16, 0, 0));
+    return __builtin_bit_cast(V4<T>, __builtin_amdgcn_raw_buffer_load_b128(r, idx * 16, 0, AUX));
   } else {
     struct H2 {
       u32x4 lo, hi;
-    } h{__builtin_amdgcn_raw_buffer_load_b128(r, idx * 32, 0, 0), __builtin_amdgcn_raw_buffer_load_b128(r, idx * 32 + 16, 0, 0)};
+    } h{__builtin_amdgcn_raw_buffer_load_b128(r, idx * 32, 0, AUX),
+        __builtin_amdgcn_raw_buffer_load_b128(r, idx * 32 + 16, 0, AUX)};
     return __builtin_bit_cast(V4<T>, h);
   }
 }
-// Stores of the stage outputs are streaming (cache policy: non-temporal):
-// the next stage reads them back from HBM anyway.
-constexpr int kStreamStore = 2;
-template <typename T>
+template <typename T, int AUX = kStream>
 __device__ __forceinline__ void bstore(__amdgpu_buffer_rsrc_t r, int idx, const V4<T>& v) {
   if constexpr (sizeof(T) == 4) {
-    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), r, idx * 16, 0, kStreamStore);
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), r, idx * 16, 0, AUX);
   } else {
     struct H2 {
       u32x4 lo, hi;
     };
     const H2 h = __builtin_bit_cast(H2, v);
-    __builtin_amdgcn_raw_buffer_store_b128(h.lo, r, idx * 32, 0, kStreamStore);
-    __builtin_amdgcn_raw_buffer_store_b128(h.hi, r, idx * 32 + 16, 0, kStreamStore);
+    __builtin_amdgcn_raw_buffer_store_b128(h.lo, r, idx * 32, 0, AUX);
+    __builtin_amdgcn_raw_buffer_store_b128(h.hi, r, idx * 32 + 16, 0, AUX);
   }
 }
 

@@ -72,6 +72,8 @@ enum StageFlags : int {
   kGrad = 256,        // wedge meshes, adjoint sweep: also accumulate the stage's gradient terms
   kTetValu = 512,     // tetrahedra: per-node dot products on the vector units (else MFMA)
   kColumnMarch = 1024,  // wedge meshes: one block marches each column (cols), with kLayerMarch
+  kStreamRes = 2048,    // stream the residual past the caches
+  kStreamU = 4096,      // stream the output state past the caches
 };
 
 // One stage over the whole mesh.  State buffers hold wedges first (Kw x Np_wedge
@@ -81,7 +83,8 @@ struct StageLaunch {
   void* Uout;
   void* res;
   const void* geo;   // wedges
-  const void* L;     // wedges: triangular operator record (lift_packed, lift_stride)
+  const void* L;     // wedges: (M^{tri,k})^-1, packed (lift_stride)
+  const void* Ln;    // wedges, node-lane kernel: L^{tri,k} column by column (node_lift_stride)
   const int* conn;
   const void* geoT;  // tetrahedra
   const int* connT;
@@ -117,17 +120,16 @@ struct StageLaunch {
   int ncols;
 };
 
-// Whether order N stores (M^{tri,k})^-1 as its lower triangle (N <= 3: kept
-// for wdg_element_data; the stage kernels factor M^{tri,k} from the geometry
-// record's vertex weights instead of reading it) instead of the lift
-// L^{tri,k} = (M^{tri,k})^-1 M^tri (Np_tri^2 values, column by column: entry
-// (r, c) at c Np_tri + r).
-constexpr bool lift_packed(int N) { return N <= 3; }
-// Per-element stride (values) of that record, padded to a multiple of 4.
+// Per-element stride (values, a multiple of 4) of the lower triangle of
+// (M^{tri,k})^-1, row by row (the level-lane stage kernels read it at the
+// orders whose mass they do not factor themselves), and of the lift
+// L^{tri,k} = (M^{tri,k})^-1 M^tri, column by column (entry (r, c) at
+// c Np_tri + r; the node-lane kernel reads it).
 int lift_stride(int N);
+int node_lift_stride(int N);
 
 hipError_t launch_setup(int N, int bits, int64_t K, const double* dX, const double* dMv, const double* dMtri,
-                        void* dGeo, void* dL, double* dAux, hipStream_t st);
+                        void* dGeo, void* dL, void* dLn, double* dAux, hipStream_t st);
 hipError_t launch_material(int bits, int64_t K, const double* dc, const double* drho, const int* dConn, void* dGeo,
                            double* dAux, hipStream_t st);
 // One stage: the mortar kernel (meshes with mortars), the wedge kernel, then
@@ -160,8 +162,12 @@ struct BatchParam {
 };
 // Elements per chunk of the wedge stage kernel (work granularity).
 int wedge_chunk_elems(int N, int bits);
+// Wavefronts per SIMD the stage kernel's registers are allocated for (idx 0:
+// single problems and the batch's first candidate) and the batch's other
+// candidate (idx 1: one fewer).
+int wedge_waves(int N, int bits, int idx);
 // One stage of every problem of order N: one block per chunk (problem, chunk)
-// of work; wpe (1 or 2) selects the register budget of the kernel.
+// of work; wpe (a wedge_waves value) selects the register budget of the kernel.
 hipError_t launch_wedge_batch(int N, int bits, const StageLaunch* probs, const int2* work, int nwork, int wpe,
                               hipStream_t st);
 // Stage s (coefficients a, b) of batch step *counter: writes the

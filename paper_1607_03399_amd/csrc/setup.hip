@@ -14,14 +14,14 @@ namespace {
 constexpr int kMaxNT = 21;
 
 template <typename T>
-__global__ void __launch_bounds__(64) setup_kernel(int NT, int LS, int64_t K, const double* __restrict__ X,
+__global__ void __launch_bounds__(64) setup_kernel(int NT, int LS, int LSN, int64_t K, const double* __restrict__ X,
                                                    const double* __restrict__ Mv, const double* __restrict__ Mtri,
-                                                   T* __restrict__ geo, T* __restrict__ L, double* __restrict__ aux) {
-  const bool packed = Mtri == nullptr;  // store (M^{tri,k})^-1 packed, else L^{tri,k}
-  __shared__ double Aug[kMaxNT * 2 * kMaxNT];
+                                                   T* __restrict__ geo, T* __restrict__ L, T* __restrict__ Ln,
+                                                   double* __restrict__ aux) {
+  __shared__ double Aug[kMaxNT * 3 * kMaxNT];
   __shared__ double fac[kMaxNT];
   const int tid = threadIdx.x;
-  const int W = 2 * NT;
+  const int W = (Ln ? 3 : 2) * NT;
   for (int64_t k = blockIdx.x; k < K; k += gridDim.x) {
     const double* x = X + k * 18;
     double xb[3], yb[3], zb[3], zt[3];
@@ -91,7 +91,7 @@ __global__ void __launch_bounds__(64) setup_kernel(int NT, int LS, int64_t K, co
       ax[6] = 0.0;
       ax[7] = 0.0;
     }
-    // [ M^{tri,k} | I ] (packed) or [ M^{tri,k} | M^tri ],
+    // [ M^{tri,k} | I ] or, where L^{tri,k} is stored too, [ M^{tri,k} | I | M^tri ],
     // M^{tri,k} = sum_v (J_tri h_v / 2) int l_a l_b lambda_v
     for (int idx = tid; idx < NT * W; idx += 64) {
       const int r = idx / W, c = idx - r * W;
@@ -99,7 +99,7 @@ __global__ void __launch_bounds__(64) setup_kernel(int NT, int LS, int64_t K, co
       if (c < NT) {
         v = cw[0] * Mv[r * NT + c] + cw[1] * Mv[NT * NT + r * NT + c] + cw[2] * Mv[2 * NT * NT + r * NT + c];
       } else {
-        v = packed ? ((c - NT == r) ? 1.0 : 0.0) : Mtri[r * NT + (c - NT)];
+        v = c < 2 * NT ? ((c - NT == r) ? 1.0 : 0.0) : Mtri[r * NT + (c - 2 * NT)];
       }
       Aug[idx] = v;
     }
@@ -118,17 +118,20 @@ __global__ void __launch_bounds__(64) setup_kernel(int NT, int LS, int64_t K, co
       }
       __syncthreads();
     }
-    // (M^{tri,k})^-1 is symmetric: its lower triangle, row by row; or L^{tri,k} column by column
+    // (M^{tri,k})^-1 is symmetric: its lower triangle, row by row; L^{tri,k} column by column
     for (int idx = tid; idx < LS; idx += 64) {
       double v = 0.0;
-      if (packed && idx < NT * (NT + 1) / 2) {
+      if (idx < NT * (NT + 1) / 2) {
         const int r = tri_row(idx), c = idx - r * (r + 1) / 2;
         v = 0.5 * (Aug[r * W + NT + c] + Aug[c * W + NT + r]);
-      } else if (!packed && idx < NT * NT) {
-        const int c = idx / NT, r = idx - c * NT;
-        v = Aug[r * W + NT + c];
       }
       L[k * LS + idx] = T(v);
+    }
+    if (Ln) {
+      for (int idx = tid; idx < LSN; idx += 64) {
+        const int c = idx / NT, r = idx - c * NT;
+        Ln[k * LSN + idx] = T(idx < NT * NT ? Aug[r * W + 2 * NT + c] : 0.0);
+      }
     }
     __syncthreads();
   }
@@ -264,23 +267,26 @@ hipError_t launch_energy_tet_t(int64_t Kt, const void* U, const double* aux, con
 
 int lift_stride(int N) {
   const int NT = (N + 1) * (N + 2) / 2;
-  return ((lift_packed(N) ? NT * (NT + 1) / 2 : NT * NT) + 3) / 4 * 4;
+  return (NT * (NT + 1) / 2 + 3) / 4 * 4;
+}
+int node_lift_stride(int N) {
+  const int NT = (N + 1) * (N + 2) / 2;
+  return (NT * NT + 3) / 4 * 4;
 }
 
 hipError_t launch_setup(int N, int bits, int64_t K, const double* dX, const double* dMv, const double* dMtri,
-                        void* dGeo, void* dL, double* dAux, hipStream_t st) {
-  if (lift_packed(N)) dMtri = nullptr;
-  else if (!dMtri) return hipErrorInvalidValue;
+                        void* dGeo, void* dL, void* dLn, double* dAux, hipStream_t st) {
+  if (dLn && !dMtri) return hipErrorInvalidValue;
   const int NT = (N + 1) * (N + 2) / 2;
-  const int LS = lift_stride(N);
+  const int LS = lift_stride(N), LSN = node_lift_stride(N);
   int64_t nb = K < 65536 ? K : 65536;
   if (nb <= 0) return hipSuccess;
   if (bits == 32)
-    hipLaunchKernelGGL(setup_kernel<float>, dim3(unsigned(nb)), dim3(64), 0, st, NT, LS, K, dX, dMv, dMtri,
-                       static_cast<float*>(dGeo), static_cast<float*>(dL), dAux);
+    hipLaunchKernelGGL(setup_kernel<float>, dim3(unsigned(nb)), dim3(64), 0, st, NT, LS, LSN, K, dX, dMv, dMtri,
+                       static_cast<float*>(dGeo), static_cast<float*>(dL), static_cast<float*>(dLn), dAux);
   else
-    hipLaunchKernelGGL(setup_kernel<double>, dim3(unsigned(nb)), dim3(64), 0, st, NT, LS, K, dX, dMv, dMtri,
-                       static_cast<double*>(dGeo), static_cast<double*>(dL), dAux);
+    hipLaunchKernelGGL(setup_kernel<double>, dim3(unsigned(nb)), dim3(64), 0, st, NT, LS, LSN, K, dX, dMv, dMtri,
+                       static_cast<double*>(dGeo), static_cast<double*>(dL), static_cast<double*>(dLn), dAux);
   return hipGetLastError();
 }
 

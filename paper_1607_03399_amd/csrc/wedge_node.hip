@@ -96,7 +96,7 @@ __device__ __forceinline__ void wedge_node_chunk(const StageLaunch& A, int chunk
   T rO[C::SO];
   {
     const auto bu = chunk_rsrc(Uin + e0 * NP, int64_t(nE) * NP * V4B);
-    const auto bl = chunk_rsrc(static_cast<const T*>(A.L) + e0 * C::LS, int64_t(nE) * C::LV * V4B);
+    const auto bl = chunk_rsrc(static_cast<const T*>(A.Ln) + e0 * C::LS, int64_t(nE) * C::LV * V4B);
     const auto bg = chunk_rsrc(static_cast<const T*>(A.geo) + e0 * kGeoStride, int64_t(nE) * C::SGV * V4B);
 #pragma unroll
     for (int k = 0; k < C::SU; ++k) rU[k] = bload<T>(bu, tid + BS * k);

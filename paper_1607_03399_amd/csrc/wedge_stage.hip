@@ -5,6 +5,7 @@
 
 #include <cmath>
 #include <type_traits>
+#include <utility>
 
 #include "device_common.hpp"
 #include "ref_tables.inc"
@@ -12,50 +13,70 @@
 namespace wdg {
 namespace {
 
-// Launch shape: one wavefront per block, lane = (element, level j), so a block
-// holds EPB = 64 / Nq elements (fewer where the LDS would exceed 64 KiB).  LDS
-// holds the staged state (per-element stride NPP, odd in 4-vectors, so that the
-// elements of a wavefront fall on different banks) and a second region that
-// first holds the inverse triangular masses, geometry records and triangular-face
-// fluxes, and afterwards the right-hand side on its way to the coalesced
-// update.
+// Highest order whose element triangular mass is factored in the block
+// (above: its stored inverse is read), and the LDS a block may take.
+#ifndef WDG_CHOL_MAX_N
+#define WDG_CHOL_MAX_N 3
+#endif
+#ifndef WDG_STAGE_LDS
+#define WDG_STAGE_LDS 81920
+#endif
+
+// Wavefronts per SIMD that the register allocation aims at, one per resident
+// block: as many blocks as the LDS of a CU holds where the registers suffice.
+#ifndef WDG_W32
+#define WDG_W32 {0, 8, 8, 6, 4, 3}
+#endif
+#ifndef WDG_W64
+#define WDG_W64 {0, 5, 4, 3, 2, 2}
+#endif
+template <int N, typename T, int MODE>
+constexpr int stage_waves() {
+  constexpr int w32[6] = WDG_W32, w64[6] = WDG_W64;
+  constexpr int a32[6] = {0, 6, 4, 3, 2, 1}, a64[6] = {0, 4, 2, 1, 1, 1};  // adjoint
+  if (MODE == 4) return sizeof(T) == 4 ? a32[N] : a64[N];
+  return sizeof(T) == 4 ? w32[N] : w64[N];
+}
+
+// Launch shape: four wavefronts per block, one per equation, all over the same
+// chunk of EPB = 64 / Nq elements (fewer where the LDS would exceed the cap);
+// lane = (element, level j).  (One wavefront with all four equations in its
+// registers ran one or two wavefronts per SIMD, and a stage of a small mesh
+// lasted its 3480 VALU instructions: with a wavefront per equation, which does
+// 1000, three to eight run per SIMD.  us per stage before and after: 128 wedges
+// at N = 3 in FP32 11.6 -> 6.8, 262 144 wedges 146 -> 142 (HBM: 688 MB at
+// 4.9 TB/s); N = 4 / 5 in FP32 on 73 728 wedges 117 / 265 -> 86 / 153 (streaming);
+// in FP64 N = 3 on 110 592 160 -> 133, N = 4 on 24 576 264 -> 70.)  LDS holds the staged state as four planes and a
+// second region that first holds the triangular operators, geometry records
+// and face fluxes, and afterwards the right-hand side, again four planes, on
+// its way to the coalesced update.
 template <int N, typename T>
 struct Cfg {
   static constexpr int NT = Dim<N>::NT, Nq = Dim<N>::Nq, NP = Dim<N>::NP;
-  static constexpr int NPP = NP | 1;
-  // N <= 3: the element's triangular mass M^{tri,k} = sum_v w_v M_v is factored
-  // (Cholesky) in the block from the vertex weights of the geometry record
-  // instead of reading a stored inverse
-  static constexpr bool CHOL = Dim<N>::PACKED;
-  static constexpr int VL = Dim<N>::LS / 4, VG = kGeoStride / 4, VF = NT;  // 4-vectors per element
-  static constexpr int XPE = (VL + VG + VF) > NPP ? (VL + VG + VF) : NPP;
-  static constexpr int per_elem = (NPP + XPE) * 4 * int(sizeof(T));
-  static constexpr int EPB_FULL = 64 / Nq;
-  static constexpr int EPB_LDS = EPB_FULL * per_elem <= 65536 ? EPB_FULL : 65536 / per_elem;
-  // Kernels that run one wavefront per SIMD (N >= 4; N = 3 in FP64, by its
-  // registers) keep all four SIMDs of a CU busy only if four blocks fit in the
-  // 160 KiB of LDS: at most 40 KiB per block (N = 5 FP32: 10 -> 9 elements,
-  // 740 -> 620 us per stage on 73 728 wedges; N = 3 FP64: 16 -> 15, 497 -> 459 us
-  // on 262 144 wedges).  With two wavefronts per SIMD (N <= 3, FP32) the same rule cost
-  // 2 % at N = 3, so there the block keeps 64 / Nq elements.
-  static constexpr bool ONE_WAVE = N >= 4 || (N == 3 && sizeof(T) == 8);
-  static constexpr int EPB_CAP = ONE_WAVE ? 40960 / per_elem : 64;
-  static constexpr int EPB = EPB_LDS < EPB_CAP ? EPB_LDS : EPB_CAP;
-  static constexpr int BS = 64;
-  // 4-vectors of the chunk each lane carries through the coalesced update
+  static constexpr int BS = 256;
+  // the element's triangular mass M^{tri,k} = sum_v w_v M_v is factored
+  // (Cholesky) in the block from the vertex weights of the geometry record;
+  // else the stored inverse (lower triangle) is read
+  static constexpr bool CHOL = N <= WDG_CHOL_MAX_N;
+  static constexpr int VL = Dim<N>::LS / 4, VLS = VL | 1;      // 4-vectors of the triangular operator, LDS stride
+  static constexpr int VG = kGeoStride / 4, VGS = VG | 1;      // of the geometry record (odd strides: banks)
+  static constexpr int XT = 4 * NT;                            // triangular-face fluxes per element
+  static constexpr int NQF = 3 * Nq * Nq;                      // quadrilateral-face nodes per element
+  static constexpr int per_elem = (4 * (VLS + VGS) + XT + 2 * NQF + 4 * NP) * int(sizeof(T));
+  // N = 2: 20 instead of 21 elements, so that chunks start on whole 128-byte
+  // lines (442 368 wedges in FP32: 123.3 -> 119.4 us per stage; at N = 4 and 5
+  // whole lines would idle a quarter of the lanes and more)
+  static constexpr int EPB_FULL = N == 2 ? 20 : 64 / Nq, EPB_CAP = WDG_STAGE_LDS / per_elem;
+  static constexpr int EPB = EPB_FULL < EPB_CAP ? EPB_FULL : EPB_CAP;
+  // 4-vectors of the chunk each lane stages and carries through the coalesced update
   static constexpr int UPD = (EPB * NP + BS - 1) / BS;
-  // Prefetch the previous residual into registers when that costs at most 40
-  // of them, or 80 for the one-wavefront-per-SIMD kernels, which have 512
-  // (per stage: N = 4 on 73 728 wedges 145 -> 131 us, N = 5 621 -> 581 us,
-  // N = 3 FP64 on 262 144 wedges 460 -> 387 us)
-#ifndef WDG_PREFETCH_REGS
-#define WDG_PREFETCH_REGS 40
-#endif
-#ifndef WDG_PREFETCH_REGS_ONE_WAVE
-#define WDG_PREFETCH_REGS_ONE_WAVE 80
-#endif
-  static constexpr bool PREFETCH =
-      UPD * 4 * int(sizeof(T)) / 4 <= (ONE_WAVE ? WDG_PREFETCH_REGS_ONE_WAVE : WDG_PREFETCH_REGS);
+  // A plane holds NP values per element without padding: at every order the
+  // lanes' NT-strided reads then fall on different banks but for pairs.  One
+  // spare value takes the lanes past the chunk.
+  static constexpr int PL = EPB * NP + 1;
+  // 4-vectors of the second region, the last one spare
+  static constexpr int XV_ = EPB * (VLS + VGS) + (EPB * (XT + 2 * NQF) + 3) / 4;
+  static constexpr int XV = (XV_ > PL ? XV_ : PL) + 1;
 };
 
 // acc1 += c x1; acc2 += c x2 for a reference-operator entry c known at
@@ -65,22 +86,13 @@ __device__ __forceinline__ void constexpr_or_skip(double c, T& acc, T x) {
   if (c != 0.0) acc += T(c) * x;
 }
 
-// entry of a reference table selected by the lane's level j (j < Nq)
-template <int Nq, typename T>
-__device__ __forceinline__ T pick(const double* tab, int j, int stride, int col) {
-  T v = T(tab[col]);
-#pragma unroll
-  for (int jj = 1; jj < Nq; ++jj) v = (j == jj) ? T(tab[jj * stride + col]) : v;
-  return v;
-}
-
-// The same selection where it is needed late in a kernel: the compiler turns
-// the selection above into one load at a selected address in global memory,
-// which is harmless next to the chunk's first loads but, issued late, comes
-// with a wait for every load still in flight.  Here the entry is the sum of the
-// entries times 0/1 masks of the lane's level (exact: one term is non-zero),
-// the masks hidden from the compiler by an empty asm statement, so that every
-// entry is read at a constant address (a scalar load).
+// Entries of the 1D operators that depend on the lane's level, as sums of
+// compile-time entries times 0/1 masks of the level (exact: one term is
+// non-zero; the masks are hidden from the compiler by an empty asm
+// statement, or it makes the selection a load at a selected address, whose
+// wait, late in a kernel, waits for every load in flight).  A table in memory
+// read with the first loads saves the sums but is one address that all
+// wavefronts read: 210 against 155 us per stage on 262 144 wedges at N = 3.
 template <int Nq, typename T>
 struct LevelMask {
   T m[Nq];
@@ -91,14 +103,62 @@ struct LevelMask {
       asm volatile("" : "+v"(m[jj]));
     }
   }
-  __device__ __forceinline__ T pick(const double* tab, int stride, int col) const {
+  // sum over the levels jj of f(jj) m[jj]; f maps an integral constant to a constant
+  template <typename F, int... J>
+  __device__ __forceinline__ T sum(F f, std::integer_sequence<int, J...>) const {
     T v = T(0);
-#pragma unroll
-    for (int jj = 0; jj < Nq; ++jj) v += m[jj] * T(tab[jj * stride + col]);
+    ((v += m[J] * f(std::integral_constant<int, J>{})), ...);
     return v;
+  }
+  template <typename F>
+  __device__ __forceinline__ T pick(F f) const {
+    return sum(f, std::make_integer_sequence<int, Nq>{});
+  }
+  // rows of a (Nq x Nq) operator: out[m] = f(j, m)
+  template <typename F, int... M>
+  __device__ __forceinline__ void rows(F f, T* out, std::integer_sequence<int, M...>) const {
+    ((out[M] = pick([f](auto jj) { return f(jj, std::integral_constant<int, M>{}); })), ...);
+  }
+  template <typename F>
+  __device__ __forceinline__ void row(F f, T* out) const {
+    rows(f, out, std::make_integer_sequence<int, Nq>{});
   }
 };
 
+// Sums of products with the rounding spelled out: left to the compiler, which
+// product is rounded before the sum may differ between the kernel's modes,
+// whose results are the same bit for bit.
+template <typename T>
+__device__ __forceinline__ T dot2(T a, T x, T b, T y) {
+  return std::fma(b, y, a * x);
+}
+template <typename T>
+__device__ __forceinline__ T dot3(T a, T x, T b, T y, T c, T z) {
+  return std::fma(c, z, dot2(a, x, b, y));
+}
+
+// 1 / x and 1 / sqrt(x) of positive normal numbers to about one unit in the
+// last place: the hardware approximation refined by Newton steps (in place of
+// the division and square root sequences, which also cover the special
+// values: 250 of the 604 instructions of the factor below at N = 3)
+__device__ __forceinline__ float inv(float x) {
+  const float r = __builtin_amdgcn_rcpf(x);
+  return std::fma(r, std::fma(-x, r, 1.0f), r);
+}
+__device__ __forceinline__ double inv(double x) {
+  double r = __builtin_amdgcn_rcp(x);
+  r = std::fma(r, std::fma(-x, r, 1.0), r);
+  return std::fma(r, std::fma(-x, r, 1.0), r);
+}
+__device__ __forceinline__ float inv_sqrt(float x) {
+  const float r = __builtin_amdgcn_rsqf(x);
+  return std::fma(0.5f * r, std::fma(-x * r, r, 1.0f), r);
+}
+__device__ __forceinline__ double inv_sqrt(double x) {
+  double r = __builtin_amdgcn_rsq(x);
+  r = std::fma(0.5 * r, std::fma(-x * r, r, 1.0), r);
+  return std::fma(0.5 * r, std::fma(-x * r, r, 1.0), r);
+}
 
 // A wedge's accumulators across the reverse sweep: FP64 sums; FP32 Kahan
 // (compensated) sums, the record holding the sums, then their compensations.
@@ -143,106 +203,89 @@ __device__ __forceinline__ void grad_record_add(void* gacc, int64_t e, const Gra
 // sig_p [p], 1/2 int sig_un [u_n] of Us weighted by the penalties'
 // derivatives (gacc slots 2..6), which the combine kernel adds up over both
 // sides of every face.  M^k = (sum_v w_v M_v) (x) M^1D and the face masses
-// are literals (reference triangle, 1D, edge masses).
-// FP32 up to N = 3 the gradient epilogue takes the element's connectivity
-// and geometry from the stage's registers and issues its gathers first and its
-// chunk loads before its first barrier: reloading them from memory after the
-// update's stores would wait for the stores.  Beyond, the extra live registers
-// spill, and it reads them from memory where they are used.
+// are literals (reference triangle, 1D, edge masses).  The wavefronts share
+// the work as the stage does: each the mass term of its field; p, u_x, u_y
+// one quadrilateral face each, u_z the triangular faces.
+//
+// Loads of the epilogue, issued before the stage's last barriers: the chunk's
+// Us (a) and forward residual (b), coalesced, the neighbour nodes of Us on the
+// wavefront's face, the wedge's accumulators; and the geometry it uses, out
+// of the stage's LDS.
 template <int N, typename T>
-constexpr bool grad_early() {
-  return sizeof(T) == 4 && N <= 3;
-}
-// the geometry the epilogue uses, copied out of the stage's LDS before the
-// right-hand side overwrites it: the lane's triangular face (bottom for level
-// 0, else top), the three quadrilateral faces, kappa, 1/rho, the vertex weights
-template <typename T>
-struct EpiGeo {
-  T tJf, tnx, tny, tnz, kap, irho, w0, w1, w2;
-  T qg[3][4];
-};
-
-// the epilogue's global loads: the quadrilateral-face neighbour nodes of Us
-// on this level, the chunk's Us (a) and forward residual (b), coalesced
-template <int N, typename T>
-struct EpiLoads {
-  static constexpr int SU = (Cfg<N, T>::EPB * Cfg<N, T>::NP + 63) / 64;
-  V4<T> gq[3][Cfg<N, T>::Nq];
-  V4<T> a[SU], b[SU];
+struct EpiData {
+  static constexpr int NT = Cfg<N, T>::NT, Nq = Cfg<N, T>::Nq;
+  V4<T> a[Cfg<N, T>::UPD], b[Cfg<N, T>::UPD];
+  int nbr, code; // across the wavefront's face (triangular: bottom for level 0, else top)
+  T fg[4];       // quadrilateral: J_f at its vertices, n_x, n_y; triangular (bottom for level 0, else top): J_f, n
+  T w0, w1, w2;  // weights of M^{tri,k}
 };
 template <int N, typename T>
-__device__ __forceinline__ void grad_load_q(const StageLaunch& A, int j, int64_t e, const int* cv, EpiLoads<N, T>& L) {
-  constexpr int NT = Cfg<N, T>::NT, Nq = Cfg<N, T>::Nq, NP = Cfg<N, T>::NP;
+__device__ __forceinline__ void grad_load(const StageLaunch& A, int64_t e0, int nE, int tid, int f, int j, int64_t e,
+                                          int tnbr, int qnbr, int code, const T* g, EpiData<N, T>& L) {
+  using C = Cfg<N, T>;
+  constexpr int NT = C::NT, Nq = C::Nq, NP = C::NP, V4B = 4 * int(sizeof(T));
   const V4<T>* __restrict__ Us = static_cast<const V4<T>*>(A.gUs);
-  const int code = cv[5];
+  const auto bb = chunk_rsrc(static_cast<const V4<T>*>(A.gRs) + e0 * NP, int64_t(nE) * NP * V4B);
+  const auto ba = chunk_rsrc(Us + e0 * NP, int64_t(nE) * NP * V4B);
 #pragma unroll
-  for (int ed = 0; ed < 3; ++ed) {
-    const int nbr = cv[2 + ed];
-    const int ned = (code >> (8 + 2 * ed)) & 3;
-    const V4<T>* nb_el = Us + (nbr >= 0 ? int64_t(nbr) : e) * NP + j * NT;
+  for (int k = 0; k < C::UPD; ++k) L.b[k] = bload<T, kStream>(bb, tid + C::BS * k);
 #pragma unroll
-    for (int q = 0; q < Nq; ++q) {
-      const int ni = ned == 0 ? edge_node(N, 0, N - q) : (ned == 1 ? edge_node(N, 1, N - q) : edge_node(N, 2, N - q));
-      L.gq[ed][q] = nb_el[ni];
-    }
-  }
-}
-template <int N, typename T>
-__device__ __forceinline__ void grad_load_chunk(const void* src, int64_t e0, int nE, int tid, V4<T>* out) {
-  constexpr int NP = Cfg<N, T>::NP, V4B = 4 * int(sizeof(T));
-  const auto br = chunk_rsrc(static_cast<const V4<T>*>(src) + e0 * NP, int64_t(nE) * NP * V4B);
+  for (int k = 0; k < C::UPD; ++k) L.a[k] = bload<T>(ba, tid + C::BS * k);
+  const int gi = f != 1 ? 20 + 4 * (f == 0 ? 0 : f - 1) : 12 + 4 * (j == 0 ? 0 : 1);
 #pragma unroll
-  for (int k = 0; k < EpiLoads<N, T>::SU; ++k) out[k] = bload<T>(br, tid + 64 * k);
+  for (int k = 0; k < 4; ++k) L.fg[k] = g[gi + k];
+  L.nbr = f != 1 ? qnbr : tnbr;
+  L.code = code;
+  L.w0 = g[37];
+  L.w1 = g[38];
+  L.w2 = g[39];
 }
 
 template <int N, typename T>
-__device__ __forceinline__ void grad_epilogue(const StageLaunch& A, int64_t e0, int nE, int tid, int le, int j,
-                                              bool active, int64_t e, V4<T>* sU, V4<T>* sX, const int* cn,
-                                              const EpiGeo<T>& eg) {
+__device__ __forceinline__ void grad_epilogue(const StageLaunch& A, int tid, int f, int le, int j, bool active,
+                                              int64_t e, T* sU, T* sX, const EpiData<N, T>& L) {
   using C = Cfg<N, T>;
   using RT = gen::RefTables<N>;
-  constexpr int NT = C::NT, Nq = C::Nq, NP = C::NP, NPP = C::NPP, EPB = C::EPB;
-  constexpr int SU = EpiLoads<N, T>::SU;
-  constexpr int GS = kGradTerms + 1;  // partial sums per lane (odd: fewer bank conflicts)
-  static_assert(EPB * 3 * Nq * Nq * 2 <= EPB * NPP * 4, "jump scratch fits the state region");
-  static_assert(EPB * Nq * GS <= EPB * C::XPE * 4, "partial sums fit the second region");
-  const bool lane_ok = le < EPB;
+  constexpr int NT = C::NT, Nq = C::Nq, NP = C::NP, EPB = C::EPB, PL = C::PL;
+  constexpr int GS = 3;  // partial sums per lane: mass term, face p, face u_n
+  static_assert(EPB * 3 * Nq * Nq * 2 <= 4 * PL, "jump scratch fits the state region");
+  static_assert(4 * EPB * Nq * GS <= 4 * PL, "partial sums fit the second region");
   const T bsign = (A.flags & kDirichlet) ? T(-1) : T(1);
-  const int lb = (lane_ok ? le : 0) * NPP + j * NT;
-  const V4<T>* __restrict__ Us = static_cast<const V4<T>*>(A.gUs);
-  constexpr bool early = grad_early<N, T>();
-  const int* __restrict__ gcn = A.conn + e * kConnStride;
-  const T* __restrict__ gm = static_cast<const T*>(A.geo) + e * kGeoStride;
-  int cv[6];
-#pragma unroll
-  for (int k = 0; k < 6; ++k) cv[k] = early ? cn[k] : gcn[k];
-  const int code = cv[5];
-  // the quadrilateral-face gathers first; FP32 up to N = 3 the chunk loads
-  // too, before the first barrier (beyond, holding them across it spills).
-  // Issuing them before the update's stores instead, so that waiting for them
-  // would not wait for the stores, measured slower (522 against 492 us per
-  // stage on 524 288 wedges)
-  EpiLoads<N, T> L;
-  grad_load_q<N, T>(A, j, e, cv, L);
-  if constexpr (early) {
-    grad_load_chunk<N, T>(A.gUs, e0, nE, tid, L.a);
-    grad_load_chunk<N, T>(A.gRs, e0, nE, tid, L.b);
-  }
-  auto slot = [&](int k) {
-    const int idx = tid + 64 * k;
-    return idx < EPB * NP ? idx + (idx / NP) * (NPP - NP) : EPB * NPP;
+  const int ed = f == 0 ? 0 : f - 1;
+  const int le0 = active ? le : 0;
+  const int lb = le0 * NP + j * NT;  // the lane's level in a plane
+  auto slot = [&](int k) { return tid + C::BS * k < EPB * NP ? tid + C::BS * k : EPB * NP; };
+  auto put = [&](T* s, int k, const V4<T>& v) {
+    const int l = slot(k);
+    s[l] = v.p;
+    s[PL + l] = v.uz;
+    s[2 * PL + l] = v.ux;
+    s[3 * PL + l] = v.uy;
   };
-  V4<T> sg[NT];
+  // own node of the wavefront's quadrilateral face
+  auto qnode = [&](int q) {
+    return lb + (ed == 0 ? edge_node(N, 0, q) : (ed == 1 ? edge_node(N, 1, q) : edge_node(N, 2, q)));
+  };
+  // sig on the wavefront's face: (p, u_n)
+  T sp[NT], sn[NT];
+  if (f != 1) {
 #pragma unroll
-  for (int i = 0; i < NT; ++i) sg[i] = sU[lb + i];
+    for (int q = 0; q < Nq; ++q) {
+      const int i = qnode(q);
+      sp[q] = sU[i];
+      sn[q] = L.fg[2] * sU[2 * PL + i] + L.fg[3] * sU[3 * PL + i];
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < NT; ++i) {
+      sp[i] = sU[lb + i];
+      sn[i] = L.fg[1] * sU[2 * PL + lb + i] + L.fg[2] * sU[3 * PL + lb + i] + L.fg[3] * sU[PL + lb + i];
+    }
+  }
   __syncthreads();  // the update and the reads of sig are done
-  if constexpr (!early) grad_load_chunk<N, T>(A.gRs, e0, nE, tid, L.b);
 #pragma unroll
-  for (int k = 0; k < SU; ++k) sU[slot(k)] = L.b[k];  // res_s over sig
+  for (int k = 0; k < C::UPD; ++k) put(sU, k, L.b[k]);  // res_s over sig
   __syncthreads();
-  T part[kGradTerms];
-#pragma unroll
-  for (int k = 0; k < kGradTerms; ++k) part[k] = T(0);
 
   // Mass terms.  The stage's right-hand side R_s enters as sig_s^T M R_s; with
   // dt R_s = res_s - a_s res_{s-1} (a_1 = 0) the sum over a step's stages equals
@@ -254,97 +297,94 @@ __device__ __forceinline__ void grad_epilogue(const StageLaunch& A, int64_t e0, 
   T m1[Nq];
   {
     const LevelMask<Nq, T> lm(j);
-#pragma unroll
-    for (int m = 0; m < Nq; ++m) m1[m] = lm.pick(RT::M1, Nq, m);
+    lm.row([](auto jj, auto m) { constexpr T v = T(RT::M1[jj * Nq + m]); return v; }, m1);
   }
-  if (lane_ok) {
-    const V4<T>* sRs = sU;
-    const V4<T>* sUa = sX;
-    const T w0 = early ? eg.w0 : gm[37], w1 = early ? eg.w1 : gm[38], w2 = early ? eg.w2 : gm[39];
-    T y[4][NT];
+  T mass = 0;
+  {
+    const T* const rs = sU + f * PL + le0 * NP;
+    const T* const ua = sX + f * PL + lb;
+    T y[NT];
 #pragma unroll
     for (int i = 0; i < NT; ++i) {
-      T a0 = 0, a1 = 0, a2 = 0, a3 = 0;
+      T s = 0;
 #pragma unroll
-      for (int m = 0; m < Nq; ++m) {
-        const V4<T> r = sRs[le * NPP + m * NT + i];
-        a0 += m1[m] * r.p;
-        a1 += m1[m] * r.ux;
-        a2 += m1[m] * r.uy;
-        a3 += m1[m] * r.uz;
-      }
-      y[0][i] = a0;
-      y[1][i] = a1;
-      y[2][i] = a2;
-      y[3][i] = a3;
+      for (int m = 0; m < Nq; ++m) s += m1[m] * rs[m * NT + i];
+      y[i] = s;
     }
-    T mp = 0, mu = 0;
+    // M^{tri,k} is symmetric: each entry is formed once and used for both
+    // rows (left to the compiler, all of them stay in registers)
+    T z[NT];
+#pragma unroll
+    for (int i = 0; i < NT; ++i) z[i] = T(0);
 #pragma unroll
     for (int i = 0; i < NT; ++i) {
-      T z0 = 0, z1 = 0, z2 = 0, z3 = 0;
+      if (i % 2 == 0) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int k = 0; k < NT; ++k) {
+      for (int k = 0; k <= i; ++k) {
         T m = 0;
-        constexpr_or_skip(RT::Mv[i * NT + k], m, w0);
-        constexpr_or_skip(RT::Mv[NT * NT + i * NT + k], m, w1);
-        constexpr_or_skip(RT::Mv[2 * NT * NT + i * NT + k], m, w2);
-        z0 += m * y[0][k];
-        z1 += m * y[1][k];
-        z2 += m * y[2][k];
-        z3 += m * y[3][k];
+        constexpr_or_skip(RT::Mv[i * NT + k], m, L.w0);
+        constexpr_or_skip(RT::Mv[NT * NT + i * NT + k], m, L.w1);
+        constexpr_or_skip(RT::Mv[2 * NT * NT + i * NT + k], m, L.w2);
+        z[i] += m * y[k];
+        if (k < i) z[k] += m * y[i];
       }
-      const V4<T> ua = sUa[lb + i];
-      mp += ua.p * z0;
-      mu += ua.ux * z1 + ua.uy * z2 + ua.uz * z3;
     }
-    part[0] = mp;
-    part[1] = mu;
+#pragma unroll
+    for (int i = 0; i < NT; ++i) mass += ua[i] * z[i];
   }
-  if constexpr (!early) grad_load_chunk<N, T>(A.gUs, e0, nE, tid, L.a);
+  // the neighbour nodes of Us on the wavefront's face, gathered here: held
+  // through the mass terms, their registers (40 at N = 3) cost a block per CU.
+  // The branches choose the nodes, the loads are common (see the stage).
+  const bool inner = L.nbr >= 0;
+  V4<T> gn[NT];
+  {
+    const V4<T>* __restrict__ Us = static_cast<const V4<T>*>(A.gUs);
+    const V4<T>* nb;
+    int off[NT];
+    if (f != 1) {
+      const int ned = (L.code >> (8 + 2 * ed)) & 3;
+      nb = Us + (inner ? int64_t(L.nbr) : e) * NP + j * NT;
+#pragma unroll
+      for (int q = 0; q < NT; ++q)
+        off[q] = q >= Nq ? 0
+                         : (ned == 0 ? edge_node(N, 0, N - q) : (ned == 1 ? edge_node(N, 1, N - q) : edge_node(N, 2, N - q)));
+    } else {
+      // lane 0 the bottom face, lane N the top one (own level); the other
+      // lanes, and boundary faces, read the own element: a valid address
+      // (one comparison for "level 0 or N": of (j == 0 || j == N) at N = 3 the
+      // compiler made a two-way switch that lost lane 0's neighbour)
+      const int tf = j == 0 ? 0 : 1;
+      const int pc = (L.code >> (3 * tf)) & 7;
+      const int nlev = ((L.code >> (6 + tf)) & 1) ? N : 0;
+      nb = Us + ((inner && j * (N - j) == 0) ? int64_t(L.nbr) : e) * NP + nlev * NT;
+#pragma unroll
+      for (int i = 0; i < NT; ++i) off[i] = face_perm<N>(pc, i);
+    }
+#pragma unroll
+    for (int i = 0; i < Nq; ++i) gn[i] = nb[off[i]];
+    if (f == 1) {
+#pragma unroll
+      for (int i = Nq; i < NT; ++i) gn[i] = nb[off[i]];
+    }
+  }
   __syncthreads();  // U~ and res_s in LDS are consumed
 #pragma unroll
-  for (int k = 0; k < SU; ++k) sX[slot(k)] = L.a[k];  // Us
+  for (int k = 0; k < C::UPD; ++k) put(sX, k, L.a[k]);  // Us
   __syncthreads();
-  const V4<T>* sUs = sX;
 
-  // triangular faces: lane 0 the bottom, lane N the top (own level).  The
-  // neighbour's face nodes are gathered here, unconditionally (the other
-  // lanes, and boundary faces, read the own element: a valid address), and
-  // used after the quadrilateral faces, which need no memory
-  const bool tri = lane_ok && (j == 0 || j == N);
-  const int face = j == 0 ? 0 : 1;
-  const int tnbr = face ? cv[1] : cv[0];
-  const bool inner = tnbr >= 0;
-  const int pc = (code >> (3 * face)) & 7;
-  const int nlev = ((code >> (6 + face)) & 1) ? N : 0;
-  const int64_t src = (tri && inner) ? int64_t(tnbr) : e;
-  V4<T> vn[NT];
-#pragma unroll
-  for (int i = 0; i < NT; ++i) vn[i] = Us[src * NP + nlev * NT + face_perm<N>(pc, i)];
-
-  // quadrilateral faces: jumps of this level (to LDS below); the adjoint
-  // trace times the edge mass stays in registers
-  T jq[3][Nq][2], ap[3][Nq], an[3][Nq];
-#pragma unroll
-  for (int ed = 0; ed < 3; ++ed) {
-    const int nbr = cv[2 + ed];
-    const T Ja = early ? eg.qg[ed][0] : gm[20 + 4 * ed], Jb = early ? eg.qg[ed][1] : gm[21 + 4 * ed];
-    const T nx = early ? eg.qg[ed][2] : gm[22 + 4 * ed], ny = early ? eg.qg[ed][3] : gm[23 + 4 * ed];
-    T sp[Nq], sn[Nq];
+  // faces: jumps of Us against the adjoint trace times the face mass
+  T fp = 0, fn = 0;
+  T ap[Nq], an[Nq];
+  if (f != 1) {
+    T jp[Nq], jn[Nq];
 #pragma unroll
     for (int q = 0; q < Nq; ++q) {
-      const int i = edge_node(N, ed, q);
-      const V4<T> own = sUs[lb + i];
-      const T pm = own.p, unm = nx * own.ux + ny * own.uy;
-      T pp = bsign * pm, unp = -bsign * unm;
-      if (nbr >= 0) {
-        pp = L.gq[ed][q].p;
-        unp = nx * L.gq[ed][q].ux + ny * L.gq[ed][q].uy;
-      }
-      jq[ed][q][0] = pp - pm;
-      jq[ed][q][1] = unp - unm;
-      sp[q] = sg[i].p;
-      sn[q] = nx * sg[i].ux + ny * sg[i].uy;
+      const int i = qnode(q);
+      const T pm = sX[i], unm = L.fg[2] * sX[2 * PL + i] + L.fg[3] * sX[3 * PL + i];
+      const T pp = inner ? gn[q].p : bsign * pm;  // else the mirror state
+      const T unp = inner ? L.fg[2] * gn[q].ux + L.fg[3] * gn[q].uy : -bsign * unm;
+      jp[q] = pp - pm;
+      jn[q] = unp - unm;
     }
 #pragma unroll
     for (int qq = 0; qq < Nq; ++qq) {
@@ -356,25 +396,29 @@ __device__ __forceinline__ void grad_epilogue(const StageLaunch& A, int64_t e0, 
         constexpr_or_skip(RT::Mb[q * Nq + qq], vpb, sp[q]);
         constexpr_or_skip(RT::Mb[q * Nq + qq], vnb, sn[q]);
       }
-      ap[ed][qq] = Ja * vpa + Jb * vpb;
-      an[ed][qq] = Ja * vna + Jb * vnb;
+      ap[qq] = L.fg[0] * vpa + L.fg[1] * vpb;
+      an[qq] = L.fg[0] * vna + L.fg[1] * vnb;
     }
-  }
-
-  if (tri) {
-    const T Jf = early ? eg.tJf : gm[12 + 4 * face], nx = early ? eg.tnx : gm[13 + 4 * face];
-    const T ny = early ? eg.tny : gm[14 + 4 * face], nz = early ? eg.tnz : gm[15 + 4 * face];
+    // the jumps to LDS [edge][wedge][level][p, u_n][node] (over res_s)
+    if (active) {
+      T* const o = sU + ((ed * EPB + le) * Nq + j) * Nq * 2;
+#pragma unroll
+      for (int q = 0; q < Nq; ++q) {
+        o[q] = jp[q];
+        o[Nq + q] = jn[q];
+      }
+    }
+  } else {
     T jp[NT], jn[NT];
 #pragma unroll
     for (int i = 0; i < NT; ++i) {
-      const V4<T> own = sUs[lb + i];
-      const T pm = own.p, unm = nx * own.ux + ny * own.uy + nz * own.uz;
-      const T pp = inner ? vn[i].p : bsign * pm;  // else the mirror state
-      const T unp = inner ? nx * vn[i].ux + ny * vn[i].uy + nz * vn[i].uz : -bsign * unm;
+      const T pm = sX[lb + i];
+      const T unm = L.fg[1] * sX[2 * PL + lb + i] + L.fg[2] * sX[3 * PL + lb + i] + L.fg[3] * sX[PL + lb + i];
+      const T pp = inner ? gn[i].p : bsign * pm;
+      const T unp = inner ? L.fg[1] * gn[i].ux + L.fg[2] * gn[i].uy + L.fg[3] * gn[i].uz : -bsign * unm;
       jp[i] = pp - pm;
       jn[i] = unp - unm;
     }
-    T sp = 0, sn = 0;
 #pragma unroll
     for (int i = 0; i < NT; ++i) {
       T mp = 0, mn = 0;
@@ -383,81 +427,84 @@ __device__ __forceinline__ void grad_epilogue(const StageLaunch& A, int64_t e0, 
         constexpr_or_skip(RT::Mtri[i * NT + k], mp, jp[k]);
         constexpr_or_skip(RT::Mtri[i * NT + k], mn, jn[k]);
       }
-      sp += sg[i].p * mp;
-      sn += (nx * sg[i].ux + ny * sg[i].uy + nz * sg[i].uz) * mn;
+      fp += sp[i] * mp;
+      fn += sn[i] * mn;
     }
-    part[2 + face] = T(0.5) * Jf * sp;
-    part[7 + face] = T(0.5) * Jf * sn;
+    fp *= T(0.5) * L.fg[0];
+    fn *= T(0.5) * L.fg[0];
   }
-
-  // the wedge's accumulator record, read before the level coupling below
-  // (idle lanes read the wedge they shadow)
+  // the wedge's accumulators, read before the level coupling
+  const bool last = f == 0 && active && j == 0;
   GradRecord<T> rec;
-  grad_record_load<T>(A.gacc, e, rec);
-  T zsum[5];  // Z- + Z+ per face
+  T kap = 0, irho = 0, zsum[5];
+  if (last) {
+    grad_record_load<T>(A.gacc, e, rec);
+    const T* gm = static_cast<const T*>(A.geo) + e * kGeoStride;
+    kap = gm[9];
+    irho = gm[10];
 #pragma unroll
-  for (int f = 0; f < 5; ++f) zsum[f] = gm[32 + f];
-  __syncthreads();  // Us in LDS is consumed
-  T* const sJ = reinterpret_cast<T*>(sU);  // quadrilateral-face jumps [wedge][edge][level][node][p, u_n]
-  if (lane_ok) {
-#pragma unroll
-    for (int ed = 0; ed < 3; ++ed)
-#pragma unroll
-      for (int q = 0; q < Nq; ++q) {
-        T* sj = sJ + (((le * 3 + ed) * Nq + j) * Nq + q) * 2;
-        sj[0] = jq[ed][q][0];
-        sj[1] = jq[ed][q][1];
-      }
+    for (int k = 0; k < 5; ++k) zsum[k] = gm[32 + k];
   }
-  __syncthreads();
-  T* const sPart = reinterpret_cast<T*>(sX);
-  if (lane_ok) {
+  __syncthreads();  // jumps complete; Us in LDS is consumed
+  if (f != 1) {
     // quadrilateral faces: couple the levels through M^1D
+    const T* const sj = sU + (ed * EPB + le0) * Nq * Nq * 2;
 #pragma unroll
-    for (int ed = 0; ed < 3; ++ed) {
-      T sp = 0, sn = 0;
+    for (int m = 0; m < Nq; ++m) {
+      T tp = 0, tn = 0;
 #pragma unroll
-      for (int m = 0; m < Nq; ++m) {
-        const T* sj = sJ + ((le * 3 + ed) * Nq + m) * Nq * 2;
-        T tp = 0, tn = 0;
-#pragma unroll
-        for (int qq = 0; qq < Nq; ++qq) {
-          tp += ap[ed][qq] * sj[2 * qq];
-          tn += an[ed][qq] * sj[2 * qq + 1];
-        }
-        sp += m1[m] * tp;
-        sn += m1[m] * tn;
+      for (int qq = 0; qq < Nq; ++qq) {
+        tp += ap[qq] * sj[m * 2 * Nq + qq];
+        tn += an[qq] * sj[m * 2 * Nq + Nq + qq];
       }
-      part[4 + ed] = T(0.5) * sp;
-      part[9 + ed] = T(0.5) * sn;
+      fp += m1[m] * tp;
+      fn += m1[m] * tn;
     }
-#pragma unroll
-    for (int k = 0; k < kGradTerms; ++k) sPart[(le * Nq + j) * GS + k] = part[k];
+    fp *= T(0.5);
+    fn *= T(0.5);
+  }
+  if (active) {
+    T* const o = sX + ((f * EPB + le) * Nq + j) * GS;
+    o[0] = mass;
+    o[1] = fp;
+    o[2] = fn;
   }
   __syncthreads();
-  if (active && j == 0) {
-    T tot[kGradTerms];
+  if (last) {
+    auto part = [&](int w, int l, int k) { return sX[((w * EPB + le) * Nq + l) * GS + k]; };
+    T mp = 0, mu = 0, tp[5], tn[5];
 #pragma unroll
-    for (int k = 0; k < kGradTerms; ++k) {
-      T s = 0;
-#pragma unroll
-      for (int l = 0; l < Nq; ++l) s += sPart[(le * Nq + l) * GS + k];
-      tot[k] = s;
+    for (int l = 0; l < Nq; ++l) {
+      mp += part(0, l, 0);
+      mu += part(1, l, 0) + part(2, l, 0) + part(3, l, 0);
     }
-    const T kap = early ? eg.kap : gm[9], irho = early ? eg.irho : gm[10];
+    tp[0] = part(1, 0, 1);
+    tn[0] = part(1, 0, 2);
+    tp[1] = part(1, N, 1);
+    tn[1] = part(1, N, 2);
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      const int w = d == 0 ? 0 : d + 1;
+      tp[2 + d] = tn[2 + d] = T(0);
+#pragma unroll
+      for (int l = 0; l < Nq; ++l) {
+        tp[2 + d] += part(w, l, 1);
+        tn[2 + d] += part(w, l, 2);
+      }
+    }
     const T c = std::sqrt(kap * irho);
     const T dt = T(A.dt);
     T x[kGradStride];
     const T gb = T(A.gb);  // dt times the mass terms' factor b_s / dt
-    x[0] = gb * T(2) / (c * kap) * tot[0];
-    x[1] = gb * (tot[0] * irho / kap + tot[1]);
+    x[0] = gb * T(2) / (c * kap) * mp;
+    x[1] = gb * (mp * irho / kap + mu);
     // per face dtau_p/dZ = -tau_p^2 / 2, dtau_u/dZ = 1/2 (upwind, tau_p = 2 / (Z- + Z+);
     // the central flux has no penalties)
     const bool upwind = !(A.flags & kCentral);
 #pragma unroll
-    for (int f = 0; f < 5; ++f) {
-      const T tp = T(2) / zsum[f];
-      x[2 + f] = upwind ? dt * (-T(0.5) * tp * tp * tot[2 + f] - T(0.5) * tot[7 + f]) : T(0);
+    for (int k = 0; k < 5; ++k) {
+      const T t = T(2) / zsum[k];
+      x[2 + k] = upwind ? dt * (-T(0.5) * t * t * tp[k] - T(0.5) * tn[k]) : T(0);
     }
     grad_record_add<T>(A.gacc, e, rec, x);
   }
@@ -466,24 +513,20 @@ __device__ __forceinline__ void grad_epilogue(const StageLaunch& A, int64_t e0, 
 // ---------------------------------------------------------------------------
 // Fused stage kernel
 //
-// Lane (element, level j) owns the triangular slice j of its element for all
-// four equations.  The reference triangle and 1D operators are compile-time
-// constants (instruction literals).  The chunk's state, lifts, geometry and
-// connectivity are staged in LDS with coalesced loads; the vertical derivative
-// and the triangle-face lifts couple the levels of one element through it.
-//   phase 1: B = -W (vertical part of D_x, D_y, D_z, before L^{tri,k}) plus the
-//            quadrilateral-face lifts of this level; triangular-face fluxes
-//   phase 2: B += triangular-face lifts; R = L^{tri,k} B + H (horizontal part);
-//            scale by kappa, 1/rho; sources
+// Lane (element, level j) of wavefront f owns the triangular slice j of its
+// element for equation f.  The reference triangle and 1D operators are
+// compile-time constants (instruction literals).  The chunk's state, geometry
+// and connectivity are staged in LDS with coalesced loads; the vertical
+// derivative and the triangle-face lifts couple the levels of one element
+// through it.
+//   phase 1: face fluxes (p, u_x, u_y: one quadrilateral face each; u_z: the
+//            triangular faces and the factor of M^{tri,k}) to LDS;
+//            B = -W (vertical part of D_x, D_y, D_z, before L^{tri,k})
+//   phase 2: B += triangular-face lifts; R = (M^{tri,k})^-1 (M^tri B +
+//            quadrilateral-face moments) + H (horizontal part); scale by
+//            kappa, 1/rho; sources
 //   update:  R goes through LDS so that the low-storage Runge-Kutta update
 //            reads and writes res and U with fully coalesced accesses
-// highest order whose quadrilateral-face fluxes are added after M^tri (edge masses)
-#ifndef WDG_QM_MAX_N
-#define WDG_QM_MAX_N 4
-#endif
-#ifndef WDG_STAGE_WAVES_PER_EU
-#define WDG_STAGE_WAVES_PER_EU 2
-#endif
 // MODE 0: wedges only; 1: tetrahedra across triangular faces; 2: also mortars;
 // 3: wedges only, vertical neighbours inside the chunk read from LDS (layer marching);
 // 4: wedges only, adjoint stage with its gradient terms (grad_epilogue);
@@ -499,486 +542,453 @@ __device__ __forceinline__ void wedge_stage_chunk(const StageLaunch& A, int64_t 
   constexpr bool MARCH = MODE == 3 || MODE == 5;
   using C = Cfg<N, T>;
   using RT = gen::RefTables<N>;
-  constexpr int NT = C::NT, Nq = C::Nq, NP = C::NP, NPP = C::NPP, EPB = C::EPB;
-  constexpr int VL = C::VL, VG = C::VG;
-  // one spare 4-vector at the end of each array takes the stores of lanes
-  // past the end of a staged stream
-  __shared__ V4<T> sU[EPB * NPP + 1];
-  __shared__ V4<T> sX[EPB * C::XPE + 1];
+  constexpr int NT = C::NT, Nq = C::Nq, NP = C::NP, EPB = C::EPB, BS = C::BS, PL = C::PL;
+  constexpr int VL = C::VL, VG = C::VG, VLS = C::VLS, GS = 4 * C::VGS, UPD = C::UPD;
+  constexpr int V4B = 4 * int(sizeof(T));
+  __shared__ T sU[4 * PL];  // planes p, u_z, u_x, u_y (the spare value of each takes the lanes past the chunk)
+  __shared__ V4<T> sX[C::XV];
   V4<T>* const sL = sX;
-  V4<T>* const sG = sX + EPB * VL;
-  T* const sF = reinterpret_cast<T*>(sG + EPB * VG);
-  V4<T>* const sR = sX;
+  T* const sG = reinterpret_cast<T*>(sX + EPB * VLS);
+  T* const sF = sG + EPB * GS;       // triangular-face fluxes [F_p, F_u][element][face][node]
+  T* const sQ = sF + EPB * C::XT;    // quadrilateral-face fluxes [F_p, F_u][element][edge][level][node]
+  T* const sR = reinterpret_cast<T*>(sX);  // right-hand side, planes as sU
 
   const V4<T>* __restrict__ Uin = static_cast<const V4<T>*>(A.Uin);
   const T* __restrict__ geo = static_cast<const T*>(A.geo);
-  const T* __restrict__ Lm = static_cast<const T*>(A.L);
   const int* __restrict__ conn = A.conn;
 
   int tid = threadIdx.x;
   // marching a column, each chunk derives its lane constants anew: hoisted
   // out of the column loop they would stay live across chunks and spill
   if constexpr (MODE == 5) asm volatile("" : "+v"(tid));
-
-  const int le = tid / Nq;
-  const int j = tid - le * Nq;
-  const bool active = tid < EPB * Nq && le < nE;
+  // the equation of this wavefront, in plane order: 0 p, 1 u_z, 2 u_x, 3 u_y
+  const int f = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int ed = f == 0 ? 0 : f - 1;  // its quadrilateral face (not for u_z)
+  const int le = lane / Nq;
+  const int j = lane - le * Nq;
+  const bool active = lane < EPB * Nq && le < nE;
   const int64_t e = e0 + (active ? le : 0);  // idle lanes shadow a valid element
   const T bsign = (A.flags & kDirichlet) ? T(-1) : T(1);
   const T tau_on = (A.flags & kCentral) ? T(0) : T(1);
-  constexpr int per = (2 * NT + Nq - 1) / Nq;  // triangular-face nodes per lane
+  // Triangular faces: the first Nq / 2 lanes of an element share out the
+  // bottom's NT nodes, the others the top's (surplus slots redo the last node)
+  constexpr int per = (NT + Nq / 2 - 1) / (Nq / 2);
+  const int face = j < Nq / 2 ? 0 : 1;
+  const int ti0 = (face ? j - Nq / 2 : j) * per;
 
   // The lane's own connectivity is read first and the neighbour gathers are
   // issued as soon as it arrives, while the chunk's coalesced staging loads
   // are still in flight: both memory latencies overlap.
-  int cn[6];
-  {
-    const int4* cp = reinterpret_cast<const int4*>(conn + e * kConnStride);
-    const int4 c0 = cp[0], c1 = cp[1];
-    cn[0] = c0.x;
-    cn[1] = c0.y;
-    cn[2] = c0.z;
-    cn[3] = c0.w;
-    cn[4] = c1.x;
-    cn[5] = c1.y;
-  }
-  constexpr int SU = (EPB * NP + 63) / 64, SL = C::CHOL ? 0 : (EPB * VL + 63) / 64, SG = (EPB * VG + 63) / 64;
-  constexpr int V4B = 4 * int(sizeof(T));
-  V4<T> rU[SU], rL[SL > 0 ? SL : 1], rG[SG];
+  // (Named values, not an array: a lane-dependent selection from a private
+  // array becomes a scratch load.)
+  const int4* cp = reinterpret_cast<const int4*>(conn + e * kConnStride);
+  const int4 c0 = cp[0], c1 = cp[1];
+  const int nb0 = c0.x, nb1 = c0.y, code = c1.y;            // across the bottom and top triangles
+  const int nbq[3] = {c0.z, c0.w, c1.x};                    // across the quadrilaterals
+  const int qnbr = ed == 0 ? nbq[0] : (ed == 1 ? nbq[1] : nbq[2]);
+  constexpr int SL = C::CHOL ? 0 : (EPB * VL + BS - 1) / BS, SG = (EPB * VG + BS - 1) / BS;
+  V4<T> rU[UPD], rL[SL > 0 ? SL : 1], rG[SG];
   {
     const auto bu = chunk_rsrc(Uin + e0 * NP, int64_t(nE) * NP * V4B);
-    const auto bl = chunk_rsrc(Lm + e0 * Dim<N>::LS, int64_t(nE) * VL * V4B);
     const auto bg = chunk_rsrc(geo + e0 * kGeoStride, int64_t(nE) * VG * V4B);
 #pragma unroll
-    for (int k = 0; k < SU; ++k) rU[k] = bload<T>(bu, tid + 64 * k);
+    for (int k = 0; k < UPD; ++k) rU[k] = bload<T>(bu, tid + BS * k);
+    if constexpr (!C::CHOL) {
+      const auto bl = chunk_rsrc(static_cast<const T*>(A.L) + e0 * Dim<N>::LS, int64_t(nE) * VL * V4B);
 #pragma unroll
-    for (int k = 0; k < SL; ++k) rL[k] = bload<T>(bl, tid + 64 * k);
-#pragma unroll
-    for (int k = 0; k < SG; ++k) rG[k] = bload<T>(bg, tid + 64 * k);
-  }
-  const int code = cn[5];
-  // quadrilateral-face neighbour nodes on this level (boundary faces read the
-  // own element, a valid address; the mirror state is blended in later)
-  V4<T> gq[3][Nq];
-#pragma unroll
-  for (int ed = 0; ed < 3; ++ed) {
-    const int nbr = cn[2 + ed];
-    const int ned = (code >> (8 + 2 * ed)) & 3;
-    const V4<T>* nb_el = Uin + (nbr >= 0 ? int64_t(nbr) : e) * NP + j * NT;
-#pragma unroll
-    for (int q = 0; q < Nq; ++q) {
-      const int ni = ned == 0 ? edge_node(N, 0, N - q) : (ned == 1 ? edge_node(N, 1, N - q) : edge_node(N, 2, N - q));
-      gq[ed][q] = nb_el[ni];
+      for (int k = 0; k < SL; ++k) rL[k] = bload<T>(bl, tid + BS * k);
     }
-  }
-  // triangular-face neighbour nodes: the 2 NT face nodes of the element are
-  // shared out over its Nq lanes (surplus slots redo the last node)
-  // Layer marching (MODE 3): a chunk is a run of consecutive layers of one
-  // column, so the wedge below or above usually sits in the same chunk; its
-  // face nodes are then read from the staged chunk after the barrier instead
-  // of being gathered from memory.
-  V4<T> gt[per];
 #pragma unroll
-  for (int t = 0; t < per; ++t) {
-    const int fraw = j * per + t;
-    const int fnode = fraw < 2 * NT ? fraw : 2 * NT - 1;
-    const int face = fnode >= NT ? 1 : 0;
-    const int i = fnode - face * NT;
-    const int nbr = face ? cn[1] : cn[0];
-    const int pc = (code >> (3 * face)) & 7;
-    const int nlev = ((code >> (6 + face)) & 1) ? N : 0;
-    const int64_t src = nbr >= 0 ? int64_t(nbr) : e;
-    const int fn = face_perm<N>(pc, i);
+    for (int k = 0; k < SG; ++k) rG[k] = bload<T>(bg, tid + BS * k);
+  }
+  const int tnbr = face ? nb1 : nb0;
+  const int tpc = (code >> (3 * face)) & 7, tlev = ((code >> (6 + face)) & 1) ? N : 0;
+  // the neighbours' face vertices in the own order (vertex permutation 0) all
+  // over the wavefront: as on meshes layered column by column
+  const bool plain = __builtin_amdgcn_ballot_w64(tpc != 0) == 0;
+  // The branches below only choose the nodes (element base and offsets); the
+  // loads are common to all wavefronts, but for the ones that the triangular
+  // faces need beyond Nq.  (Loads of both branches into one array are merged
+  // by the compiler component by component, and two arrays cost 16 registers
+  // at N = 3: on 262 144 wedges 215 and 149 us per stage.)
+  constexpr int NG = Nq > per ? Nq : per;
+  const V4<T>* nb;
+  int off[NG];
+  bool skip = false;  // layer marching: read from the staged chunk instead
+  if (f != 1) {
+    // neighbour nodes of the wavefront's quadrilateral face on this level
+    // (boundary faces read the own element, a valid address; the mirror state
+    // is blended in later)
+    const int ned = (code >> (8 + 2 * ed)) & 3;
+    nb = Uin + (qnbr >= 0 ? int64_t(qnbr) : e) * NP + j * NT;
+#pragma unroll
+    for (int q = 0; q < NG; ++q)
+      off[q] = q >= Nq ? 0
+                       : (ned == 0 ? edge_node(N, 0, N - q) : (ned == 1 ? edge_node(N, 1, N - q) : edge_node(N, 2, N - q)));
+  } else {
+    // triangular-face neighbour nodes
+    // Layer marching (MODE 3): a chunk is a run of consecutive layers of one
+    // column, so the wedge below or above usually sits in the same chunk; its
+    // face nodes are then read from the staged chunk after the barrier instead
+    // of being gathered from memory.
+    const int64_t src = tnbr >= 0 ? int64_t(tnbr) : e;
+    nb = Uin + src * NP + tlev * NT;
+    bool tet = false;
     if constexpr (HYB) {
       // a tetrahedron neighbour: its nodes follow all wedge nodes
-      const int tf = (code >> (14 + 2 * face)) & 3;
-      const bool tet = src >= A.Kw;
-      gt[t] = Uin[tet ? A.Kw * NP + (src - A.Kw) * TDim<N>::NP + tet_face_node<N>(tf, fn) : src * NP + nlev * NT + fn];
-    } else {
-      const bool in_chunk = MARCH && nbr >= 0 && src >= e0 && src < e0 + nE;
-      const bool carried = MODE == 5 && has_carry && nbr >= 0 && src == e0 - 1 && nlev == N;
-      gt[t] = V4<T>{T(0), T(0), T(0), T(0)};
-      if (!in_chunk && !carried) gt[t] = Uin[src * NP + nlev * NT + fn];
+      tet = src >= A.Kw;
+      if (tet) nb = Uin + A.Kw * NP + (src - A.Kw) * TDim<N>::NP;
+    }
+    if constexpr (MARCH) {
+      skip = (tnbr >= 0 && src >= e0 && src < e0 + nE) ||
+             (MODE == 5 && has_carry && tnbr >= 0 && src == e0 - 1 && tlev == N);
+    }
+#pragma unroll
+    for (int t = 0; t < NG; ++t) off[t] = t < per && ti0 + t < NT ? ti0 + t : NT - 1;
+    if (!plain) {
+#pragma unroll
+      for (int t = 0; t < per; ++t) off[t] = face_perm<N>(tpc, off[t]);
+    }
+    if constexpr (HYB) {
+#pragma unroll
+      for (int t = 0; t < per; ++t)
+        off[t] = tet ? tet_face_node<N>((code >> (14 + 2 * face)) & 3, off[t]) : off[t];
+    }
+  }
+  V4<T> gn[NG];
+#pragma unroll
+  for (int t = 0; t < Nq; ++t) {
+    if constexpr (MARCH) gn[t] = V4<T>{T(0), T(0), T(0), T(0)};
+    if (!MARCH || !skip) gn[t] = nb[off[t]];
+  }
+  if (f == 1) {
+#pragma unroll
+    for (int t = Nq; t < NG; ++t) {
+      if constexpr (MARCH) gn[t] = V4<T>{T(0), T(0), T(0), T(0)};
+      if (!MARCH || !skip) gn[t] = nb[off[t]];
     }
   }
 #pragma unroll
-  for (int k = 0; k < SU; ++k) {
-    const int idx = tid + 64 * k;
-    sU[idx < EPB * NP ? idx + (idx / NP) * (NPP - NP) : EPB * NPP] = rU[k];
+  for (int k = 0; k < UPD; ++k) {
+    const int idx = tid + BS * k < EPB * NP ? tid + BS * k : EPB * NP;
+    sU[idx] = rU[k].p;
+    sU[PL + idx] = rU[k].uz;
+    sU[2 * PL + idx] = rU[k].ux;
+    sU[3 * PL + idx] = rU[k].uy;
   }
 #pragma unroll
   for (int k = 0; k < SL; ++k) {
-    const int idx = tid + 64 * k;
-    sX[idx < EPB * VL ? idx : EPB * C::XPE] = rL[k];
+    const int idx = tid + BS * k;
+    sX[idx < EPB * VL ? idx + (idx / VL) * (VLS - VL) : C::XV - 1] = rL[k];
   }
 #pragma unroll
   for (int k = 0; k < SG; ++k) {
-    const int idx = tid + 64 * k;
-    sX[idx < EPB * VG ? EPB * VL + idx : EPB * C::XPE] = rG[k];
+    const int idx = tid + BS * k;
+    sX[idx < EPB * VG ? EPB * VLS + idx + (idx / VG) * (C::VGS - VG) : C::XV - 1] = rG[k];
   }
   __syncthreads();
-  if constexpr (C::CHOL) {
-    // M^{tri,k} = L L^T, row by row into the element's triangular-operator
-    // slots (entry (i, m) at i (i + 1) / 2 + m, the diagonal holding 1 / L_ii);
-    // read after the barrier that follows the triangular-face fluxes
-    if (active && j == 0) {
-      constexpr int NK = Dim<N>::NPK;
-      const T* gw = reinterpret_cast<const T*>(sG) + le * kGeoStride;
-      const T w0 = gw[37], w1 = gw[38], w2 = gw[39];
-      T a[NK];
-#pragma unroll
-      for (int f = 0; f < NK; ++f) {
-        const int i = tri_row(f), m = f - i * (i + 1) / 2;
-        T v = 0;
-        constexpr_or_skip(RT::Mv[i * NT + m], v, w0);
-        constexpr_or_skip(RT::Mv[NT * NT + i * NT + m], v, w1);
-        constexpr_or_skip(RT::Mv[2 * NT * NT + i * NT + m], v, w2);
-        a[f] = v;
-      }
-#pragma unroll
-      for (int f = 0; f < NK; ++f) {
-        const int i = tri_row(f), m = f - i * (i + 1) / 2;
-        T sm = a[f];
-#pragma unroll
-        for (int k = 0; k < m; ++k) sm -= a[i * (i + 1) / 2 + k] * a[m * (m + 1) / 2 + k];
-        a[f] = m < i ? sm * a[m * (m + 1) / 2 + m] : T(1) / std::sqrt(sm);
-      }
-      T* lo = reinterpret_cast<T*>(sL + le * VL);
-#pragma unroll
-      for (int f = 0; f < NK; ++f) lo[f] = a[f];
-    }
-  }
-  if constexpr (MARCH) {
-#pragma unroll
-    for (int t = 0; t < per; ++t) {
-      const int fraw = j * per + t;
-      const int fnode = fraw < 2 * NT ? fraw : 2 * NT - 1;
-      const int face = fnode >= NT ? 1 : 0;
-      const int nbr = face ? cn[1] : cn[0];
-      const int64_t ln = int64_t(nbr) - e0;
-      const int nlev = ((code >> (6 + face)) & 1) ? N : 0;
-      const int fn = face_perm<N>((code >> (3 * face)) & 7, fnode - face * NT);
-      if (nbr >= 0 && ln >= 0 && ln < nE) {
-        gt[t] = sU[int(ln) * NPP + nlev * NT + fn];
-      } else if (MODE == 5 && has_carry && nbr >= 0 && ln == -1 && nlev == N) {
-        gt[t] = carry[fn];
-      }
-    }
-  }
 
-  const V4<T>* el = sU + le * NPP;
-  const T* g = reinterpret_cast<const T*>(sG) + le * kGeoStride;
+  const T* const elp = sU + (active ? le : 0) * NP;  // the element's planes
+  const T* const elz = elp + PL;
+  const T* const elx = elp + 2 * PL;
+  const T* const ely = elp + 3 * PL;
+  const T* g = sG + (active ? le : 0) * GS;
 
-  // pre-lift accumulators of the four equations on this level
-  T Bp[NT], Bz[NT], Bx[NT], By[NT];
-  // Quadrilateral-face fluxes: lifted by E_e (dense Np_tri x Nq) into the
-  // pre-lift sums, or (QM) kept as (F_p, F_u) per edge node and added after the
-  // reference mass M^tri is applied, where E_e becomes the Nq x Nq edge mass
-  // on the edge's own nodes (M^tri E_e = int_edge l l_q (1 -+ xi) / 2).  QM
-  // saves VALU work where the registers for the kept fluxes are free.
-  constexpr bool QM = Dim<N>::PACKED && N <= WDG_QM_MAX_N;
-  T qf[QM ? 3 : 1][QM ? Nq : 1][2];
-
-  if (active) {
-    const T tzJ = g[4];
-    const LevelMask<Nq, T> lm(j);
-    const T tj = lm.pick(RT::t, 1, 0);
-    const T tl = T(0.5) * (T(1) - tj);
-    const T th = T(0.5) * (T(1) + tj);
-    const T txJ = g[5] * tl + g[6] * th;
-    const T tyJ = g[7] * tl + g[8] * th;
-    T dtr[Nq];
+  // face fluxes
+  if (f != 1) {
+    const T w_in = qnbr >= 0 ? T(1) : T(0);
+    const T nx = g[22 + 4 * ed], ny = g[23 + 4 * ed];
+    const T zs = g[34 + ed];  // Z- + Z+ (= 2 Z- on the boundary)
+    const T taup = tau_on * T(2) * inv(zs);
+    const T tauu = tau_on * zs * T(0.5);
+    T fp[Nq], fu[Nq];
 #pragma unroll
-    for (int m = 0; m < Nq; ++m) dtr[m] = lm.pick(RT::Dt, Nq, m);
-
-    // vertical part: W = t_dJ(t_j) (D_t U)(level j)
-#pragma unroll
-    for (int i = 0; i < NT; ++i) {
-      T dP = 0, dX = 0, dY = 0, dZ = 0;
-#pragma unroll
-      for (int m = 0; m < Nq; ++m) {
-        const V4<T> v = el[m * NT + i];
-        dP += dtr[m] * v.p;
-        dX += dtr[m] * v.ux;
-        dY += dtr[m] * v.uy;
-        dZ += dtr[m] * v.uz;
-      }
-      T w = txJ * dX;
-      w += tyJ * dY;
-      w += tzJ * dZ;
-      Bp[i] = -w;
-      Bx[i] = -(txJ * dP);
-      By[i] = -(tyJ * dP);
-      Bz[i] = -(tzJ * dP);
-    }
-
-    // quadrilateral faces (normals horizontal, so they reach p, u_x, u_y only);
-    // the mirror state of a boundary face is blended in without branches
-#pragma unroll
-    for (int ed = 0; ed < 3; ++ed) {
-      const T w_in = cn[2 + ed] >= 0 ? T(1) : T(0);
-      // a mortar face (-2 - m) takes its flux from the mortar kernel instead
-      const T Ja = MODE == 2 && cn[2 + ed] <= -2 ? T(0) : g[20 + 4 * ed];
-      const T Jb = MODE == 2 && cn[2 + ed] <= -2 ? T(0) : g[21 + 4 * ed];
-      const T nx = g[22 + 4 * ed], ny = g[23 + 4 * ed];
-      const T zs = g[34 + ed];  // Z- + Z+ (= 2 Z- on the boundary)
-      const T taup = tau_on * T(2) / zs;
-      const T tauu = tau_on * zs * T(0.5);
-      T fpa[Nq], fpb[Nq], fua[Nq], fub[Nq];
-#pragma unroll
-      for (int q = 0; q < Nq; ++q) {
-        const V4<T> own = el[j * NT + edge_node(N, ed, q)];
-        const V4<T> v = gq[ed][q];
-        const T pm = own.p;
-        const T unm = nx * own.ux + ny * own.uy;
-        // mirror state: p+ = s p-, u_n+ = -s u_n- (s = -1 Dirichlet, +1 rigid)
-        const T pb = bsign * pm, ub = -bsign * unm;
-        const T pp = pb + w_in * (v.p - pb);
-        // (u_z enters with weight zero, which keeps the gather one 16-byte load)
-        const T unp = ub + w_in * ((nx * v.ux + ny * v.uy + T(0) * v.uz) - ub);
-        const T jp = pp - pm, jun = unp - unm;
-        const T Fp = T(0.5) * (taup * jp - jun);
-        const T Fu = T(0.5) * (tauu * jun - jp);
-        if constexpr (QM) {
-          qf[ed][q][0] = Fp;
-          qf[ed][q][1] = Fu;
-        } else {
-          fpa[q] = Ja * Fp;
-          fpb[q] = Jb * Fp;
-          fua[q] = Ja * Fu;
-          fub[q] = Jb * Fu;
-        }
-      }
-      if constexpr (!QM) {
-#pragma unroll
-        for (int i = 0; i < NT; ++i) {
-          T sp = 0, su = 0;
-#pragma unroll
-          for (int q = 0; q < Nq; ++q) {
-            constexpr_or_skip(RT::Ea[(ed * NT + i) * Nq + q], sp, fpa[q]);
-            constexpr_or_skip(RT::Eb[(ed * NT + i) * Nq + q], sp, fpb[q]);
-            constexpr_or_skip(RT::Ea[(ed * NT + i) * Nq + q], su, fua[q]);
-            constexpr_or_skip(RT::Eb[(ed * NT + i) * Nq + q], su, fub[q]);
-          }
-          Bp[i] += sp;
-          Bx[i] += nx * su;
-          By[i] += ny * su;
-        }
-      }
-    }
-
-    // triangular-face fluxes (premultiplied by J_f) go to LDS for every level
-#pragma unroll
-    for (int t = 0; t < per; ++t) {
-      const int fraw = j * per + t;
-      const int fnode = fraw < 2 * NT ? fraw : 2 * NT - 1;
-      const int face = fnode >= NT ? 1 : 0;
-      const int i = fnode - face * NT;
-      const T w_in = (face ? cn[1] : cn[0]) >= 0 ? T(1) : T(0);
-      const T* gf = g + 12 + 4 * face;
-      const T Jf = gf[0], nx = gf[1], ny = gf[2], nz = gf[3];
-      const T zs = g[32 + face];
-      const T taup = tau_on * T(2) / zs;
-      const T tauu = tau_on * zs * T(0.5);
-      const V4<T> own = el[face * N * NT + i];
-      const V4<T> v = gt[t];
-      const T pm = own.p;
-      const T unm = nx * own.ux + ny * own.uy + nz * own.uz;
+    for (int q = 0; q < Nq; ++q) {
+      const int i = j * NT + (ed == 0 ? edge_node(N, 0, q) : (ed == 1 ? edge_node(N, 1, q) : edge_node(N, 2, q)));
+      const V4<T> v = gn[q];
+      const T pm = elp[i];
+      const T unm = dot2(nx, elx[i], ny, ely[i]);
+      // mirror state: p+ = s p-, u_n+ = -s u_n- (s = -1 Dirichlet, +1 rigid)
       const T pb = bsign * pm, ub = -bsign * unm;
       const T pp = pb + w_in * (v.p - pb);
-      const T unp = ub + w_in * ((nx * v.ux + ny * v.uy + nz * v.uz) - ub);
+      // (u_z enters with weight zero, which keeps the gather one 16-byte load)
+      const T unp = ub + w_in * (dot3(nx, v.ux, ny, v.uy, T(0), v.uz) - ub);
       const T jp = pp - pm, jun = unp - unm;
-      if (fraw < 2 * NT) {
-        T* f = sF + ((le * 2 + face) * NT + i) * 2;
-        f[0] = Jf * T(0.5) * (taup * jp - jun);
-        f[1] = Jf * T(0.5) * (tauu * jun - jp);
+      fp[q] = T(0.5) * (taup * jp - jun);
+      fu[q] = T(0.5) * (tauu * jun - jp);
+    }
+    if (active) {
+      T* const o = sQ + ((le * 3 + ed) * Nq + j) * Nq;
+#pragma unroll
+      for (int q = 0; q < Nq; ++q) o[q] = fp[q];
+#pragma unroll
+      for (int q = 0; q < Nq; ++q) o[EPB * C::NQF + q] = fu[q];
+    }
+  } else {
+    if constexpr (MARCH) {
+      const int64_t ln = int64_t(tnbr) - e0;
+#pragma unroll
+      for (int t = 0; t < per; ++t) {
+        const int i = ti0 + t < NT ? ti0 + t : NT - 1;
+        const int fn = face_perm<N>(tpc, i);
+        if (tnbr >= 0 && ln >= 0 && ln < nE) {
+          const T* s = sU + int(ln) * NP + tlev * NT + fn;
+          gn[t] = V4<T>{s[0], s[PL], s[2 * PL], s[3 * PL]};
+        } else if (MODE == 5 && has_carry && tnbr >= 0 && ln == -1 && tlev == N) {
+          gn[t] = carry[fn];
+        }
+      }
+    }
+    // triangular-face fluxes (premultiplied by J_f) go to LDS for every level
+    const T w_in = tnbr >= 0 ? T(1) : T(0);
+    const T* gf = g + 12 + 4 * face;
+    const T Jf = T(0.5) * gf[0], nx = gf[1], ny = gf[2], nz = gf[3];
+    const T zs = g[32 + face];
+    const T taup = tau_on * T(2) * inv(zs);
+    const T tauu = tau_on * zs * T(0.5);
+    const int own = face * N * NT;
+#pragma unroll
+    for (int t = 0; t < per; ++t) {
+      const int i = ti0 + t < NT ? ti0 + t : NT - 1;
+      const V4<T> v = gn[t];
+      const T pm = elp[own + i];
+      const T unm = dot3(nx, elx[own + i], ny, ely[own + i], nz, elz[own + i]);
+      const T pb = bsign * pm, ub = -bsign * unm;
+      const T pp = pb + w_in * (v.p - pb);
+      const T unp = ub + w_in * (dot3(nx, v.ux, ny, v.uy, nz, v.uz) - ub);
+      const T jp = pp - pm, jun = unp - unm;
+      if (active) {
+        sF[(le * 2 + face) * NT + i] = Jf * (taup * jp - jun);
+        sF[EPB * 2 * NT + (le * 2 + face) * NT + i] = Jf * (tauu * jun - jp);
+      }
+    }
+    if constexpr (C::CHOL) {
+      // M^{tri,k} = L L^T, row by row into the element's triangular-operator
+      // slots (entry (i, m) at i (i + 1) / 2 + m, the diagonal holding 1 / L_ii)
+      if (active && j == 0) {
+        constexpr int NK = Dim<N>::NPK;
+        const T w0 = g[37], w1 = g[38], w2 = g[39];
+        T a[4 * VL];
+#pragma unroll
+        for (int q = 0; q < NK; ++q) {
+          const int i = tri_row(q), m = q - i * (i + 1) / 2;
+          T v = 0;
+          constexpr_or_skip(RT::Mv[i * NT + m], v, w0);
+          constexpr_or_skip(RT::Mv[NT * NT + i * NT + m], v, w1);
+          constexpr_or_skip(RT::Mv[2 * NT * NT + i * NT + m], v, w2);
+          a[q] = v;
+        }
+#pragma unroll
+        for (int q = 0; q < NK; ++q) {
+          const int i = tri_row(q), m = q - i * (i + 1) / 2;
+          T sm = a[q];
+#pragma unroll
+          for (int k = 0; k < m; ++k) sm -= a[i * (i + 1) / 2 + k] * a[m * (m + 1) / 2 + k];
+          a[q] = m < i ? sm * a[m * (m + 1) / 2 + m] : inv_sqrt(sm);
+        }
+#pragma unroll
+        for (int q = NK; q < 4 * VL; ++q) a[q] = T(0);
+#pragma unroll
+        for (int q = 0; q < VL; ++q) sL[le * VLS + q] = V4<T>{a[4 * q], a[4 * q + 1], a[4 * q + 2], a[4 * q + 3]};
       }
     }
   }
+    // ---- phase 1, what needs no neighbour first: the gathers are still in flight
+  // pre-lift sums of the wavefront's equation on this level: vertical part
+  // W = t_dJ(t_j) (D_t U)(level j)
+  T B[NT];
+  {
+    const LevelMask<Nq, T> lm(j);
+    T dtr[Nq];
+    lm.row([](auto jj, auto m) { constexpr T v = T(RT::Dt[jj * Nq + m]); return v; }, dtr);
+    if (f == 0) {
+      const T tl = lm.pick([](auto jj) { constexpr T v = T(0.5 * (1.0 - RT::t[jj])); return v; }), th = T(1) - tl;
+      const T tzJ = g[4];
+      const T txJ = dot2(g[5], tl, g[6], th);
+      const T tyJ = dot2(g[7], tl, g[8], th);
+#pragma unroll
+      for (int i = 0; i < NT; ++i) {
+        T dX = 0, dY = 0, dZ = 0;
+#pragma unroll
+        for (int m = 0; m < Nq; ++m) {
+          dX += dtr[m] * elx[m * NT + i];
+          dY += dtr[m] * ely[m * NT + i];
+          dZ += dtr[m] * elz[m * NT + i];
+        }
+        B[i] = -dot3(txJ, dX, tyJ, dY, tzJ, dZ);
+      }
+    } else {
+      const T tl = lm.pick([](auto jj) { constexpr T v = T(0.5 * (1.0 - RT::t[jj])); return v; }), th = T(1) - tl;
+      const T tdJ = f == 1 ? g[4] : dot2(g[2 * f + 1], tl, g[2 * f + 2], th);
+#pragma unroll
+      for (int i = 0; i < NT; ++i) {
+        T dP = 0;
+#pragma unroll
+        for (int m = 0; m < Nq; ++m) dP += dtr[m] * elp[m * NT + i];
+        B[i] = -(tdJ * dP);
+      }
+    }
+  }
+
   __syncthreads();
 
-  const bool rd = (A.flags & kReadRes) != 0, wu = (A.flags & kWriteU) != 0;
   // residual of the previous stage, in the coalesced layout of the update.
   // The first stage reads none: its resource has an empty range, so the
   // loads return zeros without touching memory and need no branch.
+  const bool rd = (A.flags & kReadRes) != 0, wu = (A.flags & kWriteU) != 0;
+  const bool stream = (A.flags & kStreamRes) != 0, stream_u = (A.flags & kStreamU) != 0;
   V4<T>* const res_chunk = static_cast<V4<T>*>(A.res) + e0 * NP;
   const auto bres_in = chunk_rsrc(res_chunk, rd ? int64_t(nE) * NP * V4B : 0);
-  const auto bres = chunk_rsrc((A.flags & kResOut) ? static_cast<V4<T>*>(A.rout) + e0 * NP : res_chunk,
-                               int64_t(nE) * NP * V4B);
-  V4<T> rprev[C::PREFETCH ? C::UPD : 1];
-  if constexpr (C::PREFETCH) {
+  V4<T> rprev[UPD];
 #pragma unroll
-    for (int k = 0; k < C::UPD; ++k) rprev[k] = bload<T>(bres_in, tid + 64 * k);
-  }
+  for (int k = 0; k < UPD; ++k)
+    rprev[k] = stream ? bload<T, kStream>(bres_in, tid + BS * k) : bload<T>(bres_in, tid + BS * k);
 
-  T Rp[NT], Rz[NT], Rx[NT], Ry[NT];
-  if (active) {
+  // ---- phase 2, the same code for all equations: the flux (F_p or F_u) and
+  // the factors it is lifted with (1, or the normal's component) differ
+  T R[NT];
+  {
     // triangular-face lifts: flux spread over all levels by (M^1D)^-1 e_{0,N}
-    {
-      // exact mass: (M^1D)^-1 e_{0,N}; lumped mass (Gauss-Lobatto weights w): e_{0,N} / w_{0,N}
-      const T wend = T(0.5 * N * (N + 1));  // 1 / w_0 = 1 / w_N
-      const bool lumped = (A.flags & kLumped) != 0;
-      const LevelMask<Nq, T> lm(j);
-      const T g0j = lumped ? (j == 0 ? wend : T(0)) : lm.pick(RT::g0, 1, 0);
-      const T gNj = lumped ? (j == N ? wend : T(0)) : lm.pick(RT::gN, 1, 0);
-      const T* fbt = sF + (le * 2 + 0) * NT * 2;
-      const T* ftp = sF + (le * 2 + 1) * NT * 2;
-      const T bx = g[13], by = g[14], bz = g[15], tx = g[17], ty = g[18], tz = g[19];
+    // (exact mass) or, lumped (Gauss-Lobatto weights w), e_{0,N} / w_{0,N}
+    const T wend = T(0.5 * N * (N + 1));  // 1 / w_0 = 1 / w_N
+    const bool lumped = (A.flags & kLumped) != 0;
+    const LevelMask<Nq, T> lm(j);
+    T cb = lm.pick([](auto jj) { constexpr T v = T(RT::g0[jj]); return v; });
+    T ct = lm.pick([](auto jj) { constexpr T v = T(RT::gN[jj]); return v; });
+    if (lumped) {
+      cb = lm.m[0] * wend;
+      ct = lm.m[N] * wend;
+    }
+    if (f != 0) {
+      const int c = f == 1 ? 2 : f - 2;  // n_x, n_y, n_z
+      cb *= g[13 + c];
+      ct *= g[17 + c];
+    }
+    const T* ft = sF + (f == 0 ? 0 : EPB * 2 * NT) + (active ? le : 0) * 2 * NT;
 #pragma unroll
-      for (int i = 0; i < NT; ++i) {
-        Bp[i] += g0j * fbt[2 * i];
-        Bp[i] += gNj * ftp[2 * i];
-        const T wb = g0j * fbt[2 * i + 1], wt = gNj * ftp[2 * i + 1];
-        Bx[i] += wb * bx;
-        Bx[i] += wt * tx;
-        By[i] += wb * by;
-        By[i] += wt * ty;
-        Bz[i] += wb * bz;
-        Bz[i] += wt * tz;
-      }
+    for (int i = 0; i < NT; ++i) {
+      B[i] += cb * ft[i];
+      B[i] += ct * ft[NT + i];
     }
 
     if constexpr (MODE == 2) {
       // mortar faces: pre-lift contributions of the common refinement; the
       // buffer's range check returns zeros for the other faces
-      constexpr int NTP = (NT + 3) / 4 * 4;
-      const auto rb = chunk_rsrc(A.mortB, A.nmort * 2 * Nq * NTP * int64_t(sizeof(T)));
+      if (f != 1) {
+        constexpr int NTP = (NT + 3) / 4 * 4;
+        const auto rb = chunk_rsrc(A.mortB, A.nmort * 2 * Nq * NTP * int64_t(sizeof(T)));
 #pragma unroll
-      for (int ed = 0; ed < 3; ++ed) {
-        const int nbr = cn[2 + ed];
-        const T nxe = g[22 + 4 * ed], nye = g[23 + 4 * ed];
-        const int64_t mo = nbr <= -2 ? int64_t(-2 - nbr) : int64_t(A.nmort);
-        const int idx0 = int((mo * 2 * Nq + j) * NTP / 4);
+        for (int d = 0; d < 3; ++d) {
+          const T sc = f == 0 ? T(1) : g[22 + 4 * d + f - 2];
+          const int64_t mo = nbq[d] <= -2 ? int64_t(-2 - nbq[d]) : int64_t(A.nmort);
+          const int idx0 = int((mo * 2 * Nq + (f == 0 ? 0 : Nq) + j) * NTP / 4);
 #pragma unroll
-        for (int c = 0; c < NTP / 4; ++c) {
-          const V4<T> sp = bload<T>(rb, idx0 + c);
-          const V4<T> su = bload<T>(rb, idx0 + Nq * NTP / 4 + c);
-          const T vp[4] = {sp.p, sp.uz, sp.ux, sp.uy}, vu[4] = {su.p, su.uz, su.ux, su.uy};
+          for (int c = 0; c < NTP / 4; ++c) {
+            const V4<T> s = bload<T>(rb, idx0 + c);
+            const T v[4] = {s.p, s.uz, s.ux, s.uy};
 #pragma unroll
-          for (int kk = 0; kk < 4; ++kk) {
-            if (4 * c + kk < NT) {
-              Bp[4 * c + kk] += vp[kk];
-              Bx[4 * c + kk] += nxe * vu[kk];
-              By[4 * c + kk] += nye * vu[kk];
-            }
+            for (int k = 0; k < 4; ++k)
+              if (4 * c + k < NT) B[4 * c + k] += sc * v[k];
           }
         }
       }
     }
 
-    // triangular lift on this level, R = L^{tri,k} B with L^{tri,k} = (M^{tri,k})^-1 M^tri
-    // (Sec. 4.2).  N <= 4: the reference mass as literals, then the element's
-    // inverse mass, stored as its lower triangle (symmetric: each off-diagonal
-    // entry serves two rows); N = 5: the stored L^{tri,k}.
-    if constexpr (Dim<N>::PACKED) {
+    // R = L^{tri,k} B with L^{tri,k} = (M^{tri,k})^-1 M^tri (Sec. 4.2): the
+    // reference mass as literals, then the quadrilateral-face moments (the
+    // lift E_e before M^tri becomes the Nq x Nq edge mass on the edge's own
+    // nodes after it: M^tri E_e = int_edge l l_q (1 -+ xi) / 2), then the
+    // element's inverse mass
 #pragma unroll
-      for (int i = 0; i < NT; ++i) {
-        T sp = 0, sz = 0, sx = 0, sy = 0;
+    for (int i = 0; i < NT; ++i) {
+      T s = 0;
 #pragma unroll
-        for (int m = 0; m < NT; ++m) {
-          constexpr_or_skip(RT::Mtri[i * NT + m], sp, Bp[m]);
-          constexpr_or_skip(RT::Mtri[i * NT + m], sz, Bz[m]);
-          constexpr_or_skip(RT::Mtri[i * NT + m], sx, Bx[m]);
-          constexpr_or_skip(RT::Mtri[i * NT + m], sy, By[m]);
+      for (int m = 0; m < NT; ++m) constexpr_or_skip(RT::Mtri[i * NT + m], s, B[m]);
+      R[i] = s;
+    }
+    if (f != 1) {
+      const T* const fq = sQ + (f == 0 ? 0 : EPB * C::NQF) + ((active ? le : 0) * 3 * Nq + j) * Nq;
+#pragma unroll
+      for (int d = 0; d < 3; ++d) {
+        T Ja = g[20 + 4 * d], Jb = g[21 + 4 * d];
+        // a mortar face (-2 - m) takes its flux from the mortar kernel instead
+        if (MODE == 2 && nbq[d] <= -2) Ja = Jb = T(0);
+        if (f != 0) {
+          const T nd = g[22 + 4 * d + f - 2];
+          Ja *= nd;
+          Jb *= nd;
         }
-        Rp[i] = sp;
-        Rz[i] = sz;
-        Rx[i] = sx;
-        Ry[i] = sy;
-      }
-      if constexpr (QM) {
+        T fl[Nq];
 #pragma unroll
-        for (int ed = 0; ed < 3; ++ed) {
-          const T Ja = MODE == 2 && cn[2 + ed] <= -2 ? T(0) : g[20 + 4 * ed];
-          const T Jb = MODE == 2 && cn[2 + ed] <= -2 ? T(0) : g[21 + 4 * ed];
-          const T nx = g[22 + 4 * ed], ny = g[23 + 4 * ed];
+        for (int q = 0; q < Nq; ++q) fl[q] = fq[d * Nq * Nq + q];
+        // the edge mass J^a M^a + J^b M^b is symmetric
 #pragma unroll
-          for (int qq = 0; qq < Nq; ++qq) {
-            T pa = 0, pb = 0, ua = 0, ub = 0;
+        for (int qq = 0; qq < Nq; ++qq) {
 #pragma unroll
-            for (int q = 0; q < Nq; ++q) {
-              constexpr_or_skip(RT::Ma[qq * Nq + q], pa, qf[ed][q][0]);
-              constexpr_or_skip(RT::Mb[qq * Nq + q], pb, qf[ed][q][0]);
-              constexpr_or_skip(RT::Ma[qq * Nq + q], ua, qf[ed][q][1]);
-              constexpr_or_skip(RT::Mb[qq * Nq + q], ub, qf[ed][q][1]);
-            }
-            const T vp = Ja * pa + Jb * pb, vu = Ja * ua + Jb * ub;
-            const int i = edge_node(N, ed, qq);
-            Rp[i] += vp;
-            Rx[i] += nx * vu;
-            Ry[i] += ny * vu;
+          for (int q = 0; q <= qq; ++q) {
+            const T m = dot2(Ja, T(RT::Ma[qq * Nq + q]), Jb, T(RT::Mb[qq * Nq + q]));
+            R[edge_node(N, d, qq)] += m * fl[q];
+            if (q < qq) R[edge_node(N, d, q)] += m * fl[qq];
           }
         }
       }
-      {
-        static_assert(C::CHOL, "the packed orders factor the triangular mass");
-        // R = L^-T L^-1 R: forward substitution row by row, then the
-        // transposed solve column by column (the factor's entries in reverse)
-        const V4<T>* Lv = sL + le * VL;
-#pragma unroll
-        for (int c = 0; c < VL; ++c) {
-          const V4<T> l4 = Lv[c];
-          const T lv[4] = {l4.p, l4.uz, l4.ux, l4.uy};
-#pragma unroll
-          for (int k = 0; k < 4; ++k) {
-            const int f = 4 * c + k;
-            if (f < Dim<N>::NPK) {
-              const int i = tri_row(f), m = f - i * (i + 1) / 2;
-              if (m < i) {
-                Rp[i] -= lv[k] * Rp[m];
-                Rz[i] -= lv[k] * Rz[m];
-                Rx[i] -= lv[k] * Rx[m];
-                Ry[i] -= lv[k] * Ry[m];
-              } else {
-                Rp[i] *= lv[k];
-                Rz[i] *= lv[k];
-                Rx[i] *= lv[k];
-                Ry[i] *= lv[k];
-              }
-            }
-          }
-        }
-#pragma unroll
-        for (int c = VL - 1; c >= 0; --c) {
-          const V4<T> l4 = Lv[c];
-          const T lv[4] = {l4.p, l4.uz, l4.ux, l4.uy};
-#pragma unroll
-          for (int k = 3; k >= 0; --k) {
-            const int f = 4 * c + k;
-            if (f < Dim<N>::NPK) {
-              const int i = tri_row(f), m = f - i * (i + 1) / 2;
-              if (m < i) {
-                Rp[m] -= lv[k] * Rp[i];
-                Rz[m] -= lv[k] * Rz[i];
-                Rx[m] -= lv[k] * Rx[i];
-                Ry[m] -= lv[k] * Ry[i];
-              } else {
-                Rp[i] *= lv[k];
-                Rz[i] *= lv[k];
-                Rx[i] *= lv[k];
-                Ry[i] *= lv[k];
-              }
-            }
-          }
-        }
-      }
-    } else {
-#pragma unroll
-      for (int i = 0; i < NT; ++i) Rp[i] = Rz[i] = Rx[i] = Ry[i] = T(0);
-      const V4<T>* Lv = sL + le * VL;
+    }
+    const V4<T>* Lv = sL + (active ? le : 0) * VLS;
+    if constexpr (C::CHOL) {
+      // R = L^-T L^-1 R: forward substitution row by row, then the
+      // transposed solve column by column (the factor's entries in reverse)
+      // (no more than four 4-vectors of the operator ahead: hoisted all at
+      // once they set the kernel's register count, 99 against 82 at N = 3 and
+      // 299 against 157 at N = 4 in FP64)
 #pragma unroll
       for (int c = 0; c < VL; ++c) {
+        if (c % 4 == 0) __builtin_amdgcn_sched_barrier(0);
         const V4<T> l4 = Lv[c];
         const T lv[4] = {l4.p, l4.uz, l4.ux, l4.uy};
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-          const int f = 4 * c + k;
-          if (f < NT * NT) {
-            const int m = f / NT, i = f % NT;  // the record holds L^{tri,k} column by column
-            Rp[i] += lv[k] * Bp[m];
-            Rz[i] += lv[k] * Bz[m];
-            Rx[i] += lv[k] * Bx[m];
-            Ry[i] += lv[k] * By[m];
+          const int q = 4 * c + k;
+          if (q < Dim<N>::NPK) {
+            const int i = tri_row(q), m = q - i * (i + 1) / 2;
+            if (m < i) R[i] -= lv[k] * R[m];
+            else R[i] *= lv[k];
+          }
+        }
+      }
+#pragma unroll
+      for (int c = VL - 1; c >= 0; --c) {
+        if (c % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+        const V4<T> l4 = Lv[c];
+        const T lv[4] = {l4.p, l4.uz, l4.ux, l4.uy};
+#pragma unroll
+        for (int k = 3; k >= 0; --k) {
+          const int q = 4 * c + k;
+          if (q < Dim<N>::NPK) {
+            const int i = tri_row(q), m = q - i * (i + 1) / 2;
+            if (m < i) R[m] -= lv[k] * R[i];
+            else R[i] *= lv[k];
+          }
+        }
+      }
+    } else {
+      // the stored lower triangle of the symmetric inverse: each off-diagonal entry serves two rows
+#pragma unroll
+      for (int i = 0; i < NT; ++i) {
+        B[i] = R[i];
+        R[i] = T(0);
+      }
+#pragma unroll
+      for (int c = 0; c < VL; ++c) {
+        if (c % 4 == 0) __builtin_amdgcn_sched_barrier(0);
+        const V4<T> l4 = Lv[c];
+        const T lv[4] = {l4.p, l4.uz, l4.ux, l4.uy};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const int q = 4 * c + k;
+          if (q < Dim<N>::NPK) {
+            const int i = tri_row(q), m = q - i * (i + 1) / 2;
+            R[i] += lv[k] * B[m];
+            if (m < i) R[m] += lv[k] * B[i];
           }
         }
       }
@@ -986,117 +996,100 @@ __device__ __forceinline__ void wedge_stage_chunk(const StageLaunch& A, int64_t 
 
     // horizontal part on the own slice:
     //   R_p -= D_r (r_x u_x + r_y u_y) + D_s (s_x u_x + s_y u_y)
-    //   R_x -= r_x D_r p + s_x D_s p ;  R_y -= r_y D_r p + s_y D_s p
-    {
-      const T rx = g[0], ry = g[1], sx = g[2], sy = g[3];
-      T Ar[NT], As[NT], P[NT];
+    //   R_x -= D_r (r_x p) + D_s (s_x p) ;  R_y -= D_r (r_y p) + D_s (s_y p)
+    if (f != 1) {
+      T Ar[NT], As[NT];
+      if (f == 0) {
+        const T rx = g[0], ry = g[1], sx = g[2], sy = g[3];
 #pragma unroll
-      for (int m = 0; m < NT; ++m) {
-        const V4<T> v = el[j * NT + m];
-        Ar[m] = rx * v.ux + ry * v.uy;
-        As[m] = sx * v.ux + sy * v.uy;
-        P[m] = v.p;
+        for (int m = 0; m < NT; ++m) {
+          const T x = elx[j * NT + m], y = ely[j * NT + m];
+          Ar[m] = dot2(rx, x, ry, y);
+          As[m] = dot2(sx, x, sy, y);
+        }
+      } else {
+        const T rd_ = g[f - 2], sd = g[f];
+#pragma unroll
+        for (int m = 0; m < NT; ++m) {
+          const T p = elp[j * NT + m];
+          Ar[m] = rd_ * p;
+          As[m] = sd * p;
+        }
       }
 #pragma unroll
       for (int i = 0; i < NT; ++i) {
-        T dA = 0, dB = 0, dPr = 0, dPs = 0;
 #pragma unroll
         for (int m = 0; m < NT; ++m) {
-          constexpr_or_skip(RT::Dr[i * NT + m], dA, Ar[m]);
-          constexpr_or_skip(RT::Ds[i * NT + m], dB, As[m]);
-          constexpr_or_skip(RT::Dr[i * NT + m], dPr, P[m]);
-          constexpr_or_skip(RT::Ds[i * NT + m], dPs, P[m]);
+          constexpr_or_skip(-RT::Dr[i * NT + m], R[i], Ar[m]);
+          constexpr_or_skip(-RT::Ds[i * NT + m], R[i], As[m]);
         }
-        Rp[i] -= dA;
-        Rp[i] -= dB;
-        Rx[i] -= rx * dPr;
-        Rx[i] -= sx * dPs;
-        Ry[i] -= ry * dPr;
-        Ry[i] -= sy * dPs;
       }
     }
 
-    const T kap = g[9], irho = g[10];
+    const T scale = f == 0 ? g[9] : g[10];
 #pragma unroll
-    for (int i = 0; i < NT; ++i) {
-      Rp[i] *= kap;
-      Rz[i] *= irho;
-      Rx[i] *= irho;
-      Ry[i] *= irho;
-    }
-    for (int s = 0; s < A.nsrc; ++s) {
-      if (A.src_elem[s] == e) {
-        const T* sv = static_cast<const T*>(A.srcvec) + s * NP + j * NT;
-        const T amp = T(A.src_amp[s]);
+    for (int i = 0; i < NT; ++i) R[i] *= scale;
+    if (f == 0) {
+      for (int s = 0; s < A.nsrc; ++s) {
+        if (active && A.src_elem[s] == e) {
+          const T* sv = static_cast<const T*>(A.srcvec) + s * NP + j * NT;
+          const T amp = T(A.src_amp[s]);
 #pragma unroll
-        for (int i = 0; i < NT; ++i) Rp[i] += amp * sv[i];
+          for (int i = 0; i < NT; ++i) R[i] += amp * sv[i];
+        }
       }
     }
   }
-  // the gradient epilogue's geometry, before the right-hand side replaces it
-  [[maybe_unused]] EpiGeo<T> eg{};
-  if constexpr (MODE == 4 && grad_early<N, T>()) {
-    const T* gl = reinterpret_cast<const T*>(sG) + (le < EPB ? le : 0) * kGeoStride;
-    const int tf = j == 0 ? 0 : 1;
-    eg.tJf = gl[12 + 4 * tf];
-    eg.tnx = gl[13 + 4 * tf];
-    eg.tny = gl[14 + 4 * tf];
-    eg.tnz = gl[15 + 4 * tf];
-#pragma unroll
-    for (int ed = 0; ed < 3; ++ed)
-#pragma unroll
-      for (int k = 0; k < 4; ++k) eg.qg[ed][k] = gl[20 + 4 * ed + k];
-    eg.kap = gl[9];
-    eg.irho = gl[10];
-    eg.w0 = gl[37];
-    eg.w1 = gl[38];
-    eg.w2 = gl[39];
-  }
-  // the right-hand side replaces lifts, geometry and fluxes in LDS
+  // the gradient epilogue's loads and geometry, before the right-hand side
+  // replaces the geometry records
+  [[maybe_unused]] EpiData<N, T> ep;
+  if constexpr (MODE == 4) grad_load<N, T>(A, e0, nE, tid, f, j, e, j == 0 ? nb0 : nb1, qnbr, code, g, ep);
+  // the right-hand side replaces factors, geometry and fluxes in LDS
   __syncthreads();
   if (active) {
+    T* const o = sR + f * PL + le * NP + j * NT;
 #pragma unroll
-    for (int i = 0; i < NT; ++i) sR[le * NPP + j * NT + i] = V4<T>{Rp[i], Rz[i], Rx[i], Ry[i]};
+    for (int i = 0; i < NT; ++i) o[i] = R[i];
   }
   __syncthreads();
 
   // low-storage Runge-Kutta update, coalesced over the chunk
-  const T ca = T(A.a), cb = T(A.b), dt = T(A.dt), cg = T(A.g);
+  const T ca = T(A.a), cb = T(A.b), dt = T(A.dt), cg = (A.flags & kGamma) ? T(A.g) : T(1);
+  const auto bres = chunk_rsrc((A.flags & kResOut) ? static_cast<V4<T>*>(A.rout) + e0 * NP : res_chunk,
+                               int64_t(nE) * NP * V4B);
   const auto bout = chunk_rsrc(static_cast<V4<T>*>(A.Uout) + e0 * NP, int64_t(nE) * NP * V4B);
-  // U' = g U + b res' with g = 1 except in the adjoint sweep: two copies of the loop
-  auto update = [&](auto with_g) {
-    constexpr bool G = decltype(with_g)::value;
 #pragma unroll
-    for (int k = 0; k < C::UPD; ++k) {
-      const int idx = tid + 64 * k;
-      const int l = idx < nE * NP ? idx + (idx / NP) * (NPP - NP) : 0;
-      const V4<T> R = sR[l];
-      V4<T> q;
-      if constexpr (C::PREFETCH)
-        q = rprev[k];
-      else
-        q = bload<T>(bres_in, idx);
-      const V4<T> r{ca * q.p + dt * R.p, ca * q.uz + dt * R.uz, ca * q.ux + dt * R.ux, ca * q.uy + dt * R.uy};
-      bstore<T>(bres, idx, r);
-      // the adjoint sweep's mass terms take the incoming adjoint state from
-      // here (each slot is read above by the lane that writes it; the lanes
-      // past the chunk write the spare slot)
-      if constexpr (MODE == 4) sR[idx < nE * NP ? l : EPB * C::XPE] = q;
-      if (wu) {
-        V4<T> u = sU[l];
-        if constexpr (G) u = V4<T>{cg * u.p, cg * u.uz, cg * u.ux, cg * u.uy};
-        bstore<T>(bout, idx, V4<T>{u.p + cb * r.p, u.uz + cb * r.uz, u.ux + cb * r.ux, u.uy + cb * r.uy});
-      }
+  for (int k = 0; k < UPD; ++k) {
+    const int idx = tid + BS * k;
+    const int l = idx < EPB * NP ? idx : EPB * NP;
+    const V4<T> q = rprev[k];
+    const V4<T> r{dot2(ca, q.p, dt, sR[l]), dot2(ca, q.uz, dt, sR[PL + l]), dot2(ca, q.ux, dt, sR[2 * PL + l]),
+                  dot2(ca, q.uy, dt, sR[3 * PL + l])};
+    if (stream) bstore<T>(bres, idx, r);
+    else bstore<T, 0>(bres, idx, r);
+    // the adjoint sweep's mass terms take the incoming adjoint state from
+    // here (each slot is read above by the lane that writes it; the lanes
+    // past the chunk write the spare slot)
+    if constexpr (MODE == 4) {
+      sR[l] = q.p;
+      sR[PL + l] = q.uz;
+      sR[2 * PL + l] = q.ux;
+      sR[3 * PL + l] = q.uy;
     }
-  };
-  if (A.flags & kGamma)
-    update(std::true_type{});
-  else
-    update(std::false_type{});
-  if constexpr (MODE == 4) grad_epilogue<N, T>(A, e0, nE, tid, le, j, active, e, sU, sX, cn, eg);
+    if (wu) {
+      const V4<T> u{dot2(cg, sU[l], cb, r.p), dot2(cg, sU[PL + l], cb, r.uz), dot2(cg, sU[2 * PL + l], cb, r.ux),
+                    dot2(cg, sU[3 * PL + l], cb, r.uy)};
+      if (stream_u) bstore<T>(bout, idx, u);
+      else bstore<T, 0>(bout, idx, u);
+    }
+  }
+  if constexpr (MODE == 4) grad_epilogue<N, T>(A, tid, f, le, j, active, e, sU, sR, ep);
   if constexpr (MODE == 5) {
     __syncthreads();  // the update's reads of the staged state are done
-    if (tid < NT) carry[tid] = sU[(nE - 1) * NPP + N * NT + tid];
+    if (tid < NT) {
+      const T* s = sU + (nE - 1) * NP + N * NT + tid;
+      carry[tid] = V4<T>{s[0], s[PL], s[2 * PL], s[3 * PL]};
+    }
     __syncthreads();  // the next chunk may restage
   }
 }
@@ -1117,10 +1110,8 @@ __device__ __forceinline__ int xcd_chunk(int bid, int nb) {
   return xcd < rm ? xcd * (qd + 1) + kk : rm * (qd + 1) + (xcd - rm) * qd + kk;
 }
 
-// From N = 4 on, one wavefront per SIMD: the lane's triangle slice (15+
-// nodes x 4 equations, twice) then fits in registers instead of spilling.
 template <int N, typename T, int MODE>
-__global__ void __launch_bounds__(64, (N >= 4 ? 1 : WDG_STAGE_WAVES_PER_EU)) wedge_stage(StageLaunch A) {
+__global__ void __launch_bounds__(256, (stage_waves<N, T, MODE>())) wedge_stage(StageLaunch A) {
   wedge_stage_chunk_at<N, T, MODE>(A, xcd_chunk(blockIdx.x, gridDim.x));
 }
 
@@ -1134,7 +1125,7 @@ __global__ void __launch_bounds__(64, (N >= 4 ? 1 : WDG_STAGE_WAVES_PER_EU)) wed
 // (Straight-line code for the two chunks: a loop over chunks keeps values
 // live across its back edge and spills.)
 template <int N, typename T>
-__global__ void __launch_bounds__(64, (N >= 4 ? 1 : WDG_STAGE_WAVES_PER_EU)) wedge_column_stage(StageLaunch A) {
+__global__ void __launch_bounds__(256, (stage_waves<N, T, 5>())) wedge_column_stage(StageLaunch A) {
   constexpr int EPB = Cfg<N, T>::EPB;
   __shared__ V4<T> carry[Dim<N>::NT];
   const int2 col = A.cols[xcd_chunk(blockIdx.x, gridDim.x)];
@@ -1150,11 +1141,10 @@ __global__ void __launch_bounds__(64, (N >= 4 ? 1 : WDG_STAGE_WAVES_PER_EU)) wed
 // of it (face neighbours share an L2).  The stage record of each problem
 // (buffers, coefficients, time step, source amplitudes) is in device memory,
 // written by the batch preparation kernel of the stage.  WPE is the
-// occupancy the register allocation aims at (1: up to 512 registers, no
-// spills at high order; 2: as the single-problem kernel), chosen per order by
-// the batch autotuner.
+// occupancy the register allocation aims at, chosen per order by the batch
+// autotuner.
 template <int N, typename T, int WPE>
-__global__ void __launch_bounds__(64, WPE)
+__global__ void __launch_bounds__(256, WPE)
     wedge_batch_stage(const StageLaunch* __restrict__ probs, const int2* __restrict__ work, int nwork) {
   const int w = xcd_chunk(blockIdx.x, gridDim.x);
   if (w >= nwork) return;
@@ -1165,12 +1155,13 @@ __global__ void __launch_bounds__(64, WPE)
 template <int N, typename T>
 hipError_t launch_wedge_batch_t(const StageLaunch* probs, const int2* work, int nwork, int wpe, hipStream_t st) {
   if (nwork <= 0) return hipSuccess;
-  if (wpe == 1)
-    hipLaunchKernelGGL((wedge_batch_stage<N, T, 1>), dim3(unsigned(nwork)), dim3(Cfg<N, T>::BS), 0, st, probs, work,
+  constexpr int W = stage_waves<N, T, 0>();
+  if (wpe == W)
+    hipLaunchKernelGGL((wedge_batch_stage<N, T, W>), dim3(unsigned(nwork)), dim3(Cfg<N, T>::BS), 0, st, probs, work,
                        nwork);
   else
-    hipLaunchKernelGGL((wedge_batch_stage<N, T, 2>), dim3(unsigned(nwork)), dim3(Cfg<N, T>::BS), 0, st, probs, work,
-                       nwork);
+    hipLaunchKernelGGL((wedge_batch_stage<N, T, W - 1>), dim3(unsigned(nwork)), dim3(Cfg<N, T>::BS), 0, st, probs,
+                       work, nwork);
   return hipGetLastError();
 }
 
@@ -1202,6 +1193,14 @@ int wedge_chunk_elems(int N, int bits) {
   WDG_DISPATCH_N(N, bits, WDG_EPB)
 #undef WDG_EPB
   return epb;
+}
+
+int wedge_waves(int N, int bits, int idx) {
+  int w = 0;
+#define WDG_WAVES(n, T) w = stage_waves<n, T, 0>()
+  WDG_DISPATCH_N(N, bits, WDG_WAVES)
+#undef WDG_WAVES
+  return w - (idx ? 1 : 0);
 }
 
 hipError_t launch_wedge_batch(int N, int bits, const StageLaunch* probs, const int2* work, int nwork, int wpe,

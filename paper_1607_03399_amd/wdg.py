@@ -231,8 +231,8 @@ class Solver:
         self._check(self._lib.wdg_set_tet_kernel(self._h, {"mfma": 0, "valu": 1}[variant]), "set_tet_kernel")
 
     def set_wedge_kernel(self, variant: str):
-        """'auto' (default: one lane per triangle node in FP32 at orders 4 and 5, else one lane per
-        GLL level),
+        """'auto' (default: one lane per GLL level; at orders 4 and 5 in FP32 one lane per triangle
+        node on meshes of fewer than 32 wedges),
         'level' (one lane per GLL level) or 'node' (one lane per triangle node wherever it exists)."""
         self._check(self._lib.wdg_set_wedge_kernel(self._h, {"auto": 0, "level": 1, "node": 2}[variant]),
                     "set_wedge_kernel")
