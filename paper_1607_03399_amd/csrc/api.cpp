@@ -432,8 +432,19 @@ bool node_kernel(const wdg_ctx* ctx, int flags) {
   return ctx->wedge_kernel == WDG_WEDGE_NODE || (ctx->wedge_kernel == WDG_WEDGE_AUTO && ctx->Kw < kNodeAutoWedges);
 }
 
-// Cache policy of a stage: the residual and the output state stream past the caches.
-int stream_flags(size_t, size_t) { return wdg::kStreamRes | wdg::kStreamU; }
+// Cache policy of a stage over state buffers of state_bytes each (two states
+// and the residual) and record_bytes of element records.  What fits the 256
+// MiB Infinity Cache is left to it, the rest streams past the caches: nothing,
+// the residual, or residual and output state.  us per stage, nothing / residual
+// / both streamed: order 3 FP32, 106 496 wedges (215 MiB in all) 51 / - / 63;
+// 122 880 (248 MiB; without the residual 173) 77 / 64 / 71; 155 648 (219 without)
+// 99 / 77 / 88; 188 416 (265 without) 117 / 120 / 105; order 1, 1 048 576 wedges
+// (384 without) - / 117 / 110.
+int stream_flags(size_t state_bytes, size_t record_bytes) {
+  const size_t MiB = size_t(1) << 20;
+  return (3 * state_bytes + record_bytes > 232 * MiB ? wdg::kStreamRes : 0) |
+         (2 * state_bytes + record_bytes > 250 * MiB ? wdg::kStreamU : 0);
+}
 size_t state_bytes(const wdg_ctx* ctx) { return size_t(ctx->nodes()) * 4 * ctx->tsize(); }
 size_t record_bytes(const wdg_ctx* ctx) {
   return size_t(ctx->Kw) * (wdg::kGeoStride * ctx->tsize() + wdg::kConnStride * sizeof(int)) +

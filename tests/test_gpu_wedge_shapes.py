@@ -1,14 +1,17 @@
-"""Edges of the level-lane wedge kernel's launch shapes and of the rule that
-chooses a kernel by the mesh size: element counts around a block's chunk
-against the FP64 oracle (relative L2 1e-12 in FP64, 1e-5 in FP32), the line
-between the wedge kernels, and a batch on both sides of it."""
+"""Edges of the level-lane wedge kernel's launch shapes and of the rules that
+choose a kernel or a cache policy by the mesh size: element counts around a
+block's chunk against the FP64 oracle (relative L2 1e-12 in FP64, 1e-5 in
+FP32), the line between the wedge kernels, a batch on both sides of it, and a
+state whose residual alone is streamed past the caches against the FP64 solve
+(10 steps add the rounding of 50 stages, below 1e-5 as a single right-hand
+side's)."""
 import numpy as np
 import pytest
 
 from oracle import dg
 from paper_1607_03399_amd import inputs
 from paper_1607_03399_amd import wdg
-from parity import TOL, check
+from parity import TOL, check, rel
 
 pytestmark = pytest.mark.gpu
 
@@ -82,3 +85,19 @@ def test_batch_on_both_kernels_of_an_order():
     batch.close()
     for s in solvers + alone:
         s.close()
+
+
+def test_streamed_residual_alone():
+    """114 688 wedges at N = 3 in FP32 (220 MiB of state and residual: the
+    residual streams, the states stay cached) against the FP64 solve."""
+    m = inputs.layered_config(64, 14, 0.3, seed=2)
+    out = []
+    for bits in (64, 32):
+        s = _solver(m, 3, bits)
+        U = np.zeros((s.K, 4, s.NPmax))
+        U[:, 0] = inputs.gaussian_pulse(s.node_coords(), width=0.2)
+        s.set_fields(U)
+        s.step(10, s.stable_dt(0.5))
+        out.append(s.get_fields())
+        s.close()
+    assert rel(out[1], out[0]) <= TOL[32]
