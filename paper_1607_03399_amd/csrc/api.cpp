@@ -599,6 +599,26 @@ std::vector<double> mortar_tables(const RefOps& R) {
     for (int i = 0; i < NT; ++i)
       for (int q = 0; q < Nq; ++q) out.push_back(MtriInv[i * NT + R.edge_nodes[e][q]]);
   out.insert(out.end(), MtriInv.begin(), MtriInv.end());
+  // (M^tri)^-1 at the nodes of edge e times the edge masses weighted by either
+  // end's linear function (exact: degree 2N + 1)
+  std::vector<double> xg, wg, l(Nq);
+  wdg::gauss_legendre(Nq + 1, xg, wg);
+  for (int end = 0; end < 2; ++end) {
+    std::vector<double> E(Nq * Nq, 0.0);
+    for (size_t a = 0; a < xg.size(); ++a) {
+      R.line_basis(xg[a], l.data());
+      const double w = wg[a] * 0.5 * (end ? 1.0 + xg[a] : 1.0 - xg[a]);
+      for (int q = 0; q < Nq; ++q)
+        for (int r = 0; r < Nq; ++r) E[q * Nq + r] += w * l[q] * l[r];
+    }
+    for (int e = 0; e < 3; ++e)
+      for (int i = 0; i < NT; ++i)
+        for (int r = 0; r < Nq; ++r) {
+          double v = 0.0;
+          for (int q = 0; q < Nq; ++q) v += MtriInv[i * NT + R.edge_nodes[e][q]] * E[q * Nq + r];
+          out.push_back(v);
+        }
+  }
   return out;
 }
 
@@ -687,6 +707,24 @@ std::vector<double> mortar_cores(const RefOps& R, const std::vector<MortarHost>&
       if (m0 < m1) pool.emplace_back(work, m0, m1);
     }
     for (auto& th : pool) th.join();
+  }
+  return out;
+}
+
+// The blocks of mortar_cores that the device keeps (wdg::mort_dev_stride)
+std::vector<double> mortar_blocks(int N, const std::vector<double>& cores) {
+  const int NT = (N + 1) * (N + 2) / 2, NW = (N + 1) * (N + 1), n = wdg::mort_core_n(N), NPK = n * (n + 1) / 2;
+  const size_t CS = wdg::mort_core_stride(N), DS = wdg::mort_dev_stride(N), nm = cores.size() / CS;
+  std::vector<double> out(nm * DS, 0.0);
+  for (size_t m = 0; m < nm; ++m) {
+    const double* C = &cores[m * CS];
+    double* o = &out[m * DS];
+    auto at = [n](int c, int r) { return c * n - c * (c - 1) / 2 + r - c; };
+    for (int c = 0; c < NW; ++c)
+      for (int r = c; r < NW; ++r) *o++ = C[at(c, r)];
+    for (int side = 0; side < 2; ++side)
+      for (int i = 0; i < NT; ++i)
+        for (int c = 0; c < NW; ++c) *o++ = C[size_t(side) * NPK + at(c, NW + i)];
   }
   return out;
 }
@@ -1256,7 +1294,7 @@ int wdg_set_mesh(wdg_ctx* ctx, int64_t nv, const double* vxyz, int64_t nw, const
     const std::vector<double> tabs = mortar_tables(R);
     if (int(tabs.size()) != wdg::mortar_table_size(ctx->N)) return fail(ctx, WDG_ERR_HIP, "mortar table layout");
     const std::vector<unsigned char> tabT = to_precision(tabs, ctx->bits);
-    const std::vector<unsigned char> cores = to_precision(mortar_cores(R, ctx->mort), ctx->bits);
+    const std::vector<unsigned char> cores = to_precision(mortar_blocks(ctx->N, mortar_cores(R, ctx->mort)), ctx->bits);
     HIPCHK(hipMalloc(&ctx->dMortI, mi.size() * sizeof(int32_t)));
     HIPCHK(hipMalloc(&ctx->dMortG, nm * wdg::kMortGeoStride * sizeof(double)));
     HIPCHK(hipMalloc(&ctx->dMortTab, tabT.size()));

@@ -59,6 +59,13 @@ __host__ __device__ constexpr int mort_core_n(int N) { return (N + 1) * (N + 1) 
 __host__ __device__ constexpr int mort_core_stride(int N) {
   return (mort_core_n(N) * (mort_core_n(N) + 1) + 3) / 4 * 4;
 }
+// What the device keeps of them: the wedge-wedge block of side 0 (lower
+// triangle, packed by columns), then of each side the wedge-tetrahedron block
+// (tetrahedron node by tetrahedron node), padded to a multiple of 4 values.
+__host__ __device__ constexpr int mort_dev_stride(int N) {
+  const int NW = (N + 1) * (N + 1), NT = (N + 1) * (N + 2) / 2;
+  return (NW * (NW + 1) / 2 + 2 * NW * NT + 3) / 4 * 4;
+}
 
 enum StageFlags : int {
   kReadRes = 1,    // res = a res + dt rhs (else res = dt rhs)
@@ -94,7 +101,7 @@ struct StageLaunch {
   const int* mortI;    // mortars: kMortIntStride ints each
   const void* mortG;   // kMortGeoStride FP64 values each
   const void* mortTab; // reference tables of the mortar outputs, type T (see mortar_table_size)
-  const void* mortC;   // per mortar: mort_core_stride values of type T (coupling matrices)
+  const void* mortC;   // per mortar: mort_dev_stride values of type T (coupling matrices)
   void* mortB;         // per mortar: wedge pre-lift contributions [p, u][Nq][Np_tri padded to 4]
   void* mortF;         // per mortar side: equivalent nodal tetrahedron-face flux [p, u][Np_tri]
   int64_t nmort;
