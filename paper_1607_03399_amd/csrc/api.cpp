@@ -1254,7 +1254,7 @@ int wdg_set_mesh(wdg_ctx* ctx, int64_t nv, const double* vxyz, int64_t nw, const
     HIPCHK(hipMalloc(&ctx->dGeoT, size_t(Kt) * wdg::kTetGeoStride * ts));
     HIPCHK(hipMalloc(&ctx->dConnT, size_t(Kt) * wdg::kTetConnStride * sizeof(int32_t)));
     HIPCHK(hipMalloc(&ctx->dAuxT, size_t(Kt) * wdg::kTetAuxStride * sizeof(double)));
-    const size_t nops = 3 * size_t(NPt) * NPt + size_t(NPt) * 4 * NT;
+    const size_t nops = size_t(wdg::tet_ops_size(ctx->N));
     HIPCHK(hipMalloc(&ctx->dOpsT, nops * ts));
     HIPCHK(hipMalloc(&ctx->dMt, size_t(NPt) * NPt * sizeof(double)));
     std::vector<double> ops;
@@ -1263,11 +1263,21 @@ int wdg_set_mesh(wdg_ctx* ctx, int64_t nv, const double* vxyz, int64_t nw, const
     ops.insert(ops.end(), Tt.Ds.begin(), Tt.Ds.end());
     ops.insert(ops.end(), Tt.Dt.begin(), Tt.Dt.end());
     ops.insert(ops.end(), Tt.LIFT.begin(), Tt.LIFT.end());
-    std::vector<unsigned char> buf(nops * ts);
-    for (size_t i = 0; i < nops; ++i) {
-      if (ctx->bits == 32) reinterpret_cast<float*>(buf.data())[i] = float(ops[i]);
-      else reinterpret_cast<double*>(buf.data())[i] = ops[i];
+    ops.resize(nops, 0.0);
+    {
+      const int KV = (NPt + 3) / 4, FN = 4 * NT, S = wdg::tet_frag_steps(ctx->N);
+      const std::vector<double>* mats[4] = {&Tt.Dr, &Tt.Ds, &Tt.Dt, &Tt.LIFT};
+      double* frag = &ops[size_t(wdg::tet_row_ops(ctx->N))];
+      for (int w = 0; w < (NPt + 15) / 16; ++w)
+        for (int s = 0; s < 3 * KV + (FN + 3) / 4; ++s)
+          for (int lane = 0; lane < 64; ++lane) {
+            const int o = s < 3 * KV ? s / KV : 3, cols = o < 3 ? NPt : FN;
+            const int row = 16 * w + lane % 16, col = 4 * (s - o * KV) + lane / 16;
+            if (row < NPt && col < cols)
+              frag[((size_t(w) * S / 4 + s / 4) * 64 + lane) * 4 + s % 4] = (*mats[o])[size_t(row) * cols + col];
+          }
     }
+    const std::vector<unsigned char> buf = to_precision(ops, ctx->bits);
     HIPCHK(hipMemcpyAsync(ctx->dOpsT, buf.data(), buf.size(), hipMemcpyHostToDevice, ctx->stream));
     HIPCHK(hipMemcpyAsync(ctx->dMt, Tt.M.data(), Tt.M.size() * sizeof(double), hipMemcpyHostToDevice, ctx->stream));
     HIPCHK(hipMemcpyAsync(ctx->dConnT, ctx->connT.data(), ctx->connT.size() * sizeof(int32_t), hipMemcpyHostToDevice,

@@ -67,6 +67,23 @@ __host__ __device__ constexpr int mort_dev_stride(int N) {
   return (NW * (NW + 1) / 2 + 2 * NW * NT + 3) / 4 * 4;
 }
 
+// Tetrahedron operators on the device: Dr, Ds, Dt (Np x Np each) and LIFT
+// (Np x 4 Np_tri), padded to a multiple of 4 values, then the same as MFMA A
+// operands: per row tile of 16 and 4 consecutive k-steps (of Dr, Ds, Dt, LIFT
+// one after the other), 4 values per lane, zeros outside the operators.
+__host__ __device__ constexpr int tet_row_ops(int N) {
+  const int NP = (N + 1) * (N + 2) * (N + 3) / 6, FN = 2 * (N + 1) * (N + 2);
+  return (3 * NP * NP + NP * FN + 3) / 4 * 4;
+}
+__host__ __device__ constexpr int tet_frag_steps(int N) {  // k-steps of 4 columns, padded to a multiple of 4
+  const int NP = (N + 1) * (N + 2) * (N + 3) / 6, FN = 2 * (N + 1) * (N + 2);
+  return (3 * ((NP + 3) / 4) + (FN + 3) / 4 + 3) / 4 * 4;
+}
+__host__ __device__ constexpr int tet_ops_size(int N) {
+  const int NP = (N + 1) * (N + 2) * (N + 3) / 6;
+  return tet_row_ops(N) + (NP + 15) / 16 * tet_frag_steps(N) * 64;
+}
+
 enum StageFlags : int {
   kReadRes = 1,    // res = a res + dt rhs (else res = dt rhs)
   kWriteU = 2,     // U_out = U_in + b res
@@ -95,7 +112,7 @@ struct StageLaunch {
   const int* conn;
   const void* geoT;  // tetrahedra
   const int* connT;
-  const void* opsT;  // tetrahedron operators: Dr, Ds, Dt (Np x Np each), LIFT (Np x 4 Np_tri)
+  const void* opsT;  // tetrahedron operators (see tet_ops_size)
   const void* opsW;  // N >= 4 wedges: reference rows D_r, D_s (Np_tri x Np_tri), E^a, E^b ([edge][Np_tri][N+1])
   const void* srcvec;  // kMaxSources x Np_wedge (a tetrahedron source uses the first Np_tet)
   const int* mortI;    // mortars: kMortIntStride ints each

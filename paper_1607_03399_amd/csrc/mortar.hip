@@ -29,10 +29,10 @@ namespace {
 //   tetrahedra:  equivalent nodal face flux (M^tri)^-1 (moments) / (area / 2)
 // Bound by the blocks' bytes: at N = 4 in FP32 a mortar reads 4.3 KB of them
 // (6.6 KB with all six) of 6.0 KB in all.  us per stage of hybrid meshes with
-// all six and with three, whose wedge and tetrahedron kernels are the same:
-// 39 312 wedges, 29 520 tetrahedra and 23 232 mortars at N = 4 in FP32
-// 143.9 -> 129.6; 25 792 elements at N = 5 in FP32 117.8 -> 107.7, at N = 4 in
-// FP64 135.9 -> 121.0; 68 784 at N = 2 in FP32 48.3 -> 45.8.
+// all six and with three: 39 312 wedges, 29 520 tetrahedra and 23 232 mortars
+// at N = 4 in FP32 137.8 -> 130.3 (the kernel itself 48 -> 38); 25 792 elements
+// at N = 5 in FP32 115.8 -> 107.9, at N = 4 in FP64 131.6 -> 121.0; 154 800 at
+// N = 3 in FP32 166 -> 151.
 // One wavefront per mortar.
 // ---------------------------------------------------------------------------
 template <int N>

@@ -289,7 +289,17 @@ struct MCfg {
   static constexpr int RT = (NP + 15) / 16;  // row tiles: one wavefront each
   static constexpr int BS = 64 * RT;
   // tetrahedra per chunk: the (p, o.u) column pairs fill whole 16-column tiles
-  static constexpr int EPB = N <= 2 ? 16 : 8;
+  // (16 at N <= 2 take the LDS of twice the wavefronts: 46.0 against 44.0 us
+  // per hybrid stage of 68 784 elements at N = 2 in FP32)
+  static constexpr int EPB = 8;
+  // The lanes' indices into a chunk, left to the compiler, are computed once
+  // and held over all chunks in up to 90 registers; computed for every chunk
+  // they leave room for one more wavefront per SIMD.  At N = 4 and 5 in FP32
+  // the registers are the cheaper side (us per hybrid stage held / computed:
+  // N = 4 FP32 128 / 136, N = 5 FP32 99 / 100; N = 3 FP32 within 2 us of 150, N = 4
+  // FP64 120 / 113, N = 3 FP64 64.8 / 63.1).
+  static constexpr bool HELD = N >= 4 && sizeof(T) == 4;
+  static constexpr int WPE = HELD ? 1 : (sizeof(T) == 4 ? 3 : 2);
   static constexpr int KV = (NP + 3) / 4, KL = (FN + 3) / 4;  // k-steps
   static constexpr int VCT = 2 * EPB / 16, LCT = 4 * EPB / 16;  // column tiles
   static constexpr int NN = EPB * NP, NPL = (NN + BS - 1) / BS;  // nodes per lane
@@ -299,7 +309,7 @@ struct MCfg {
 };
 
 template <int N, typename T>
-__global__ void __launch_bounds__((MCfg<N, T>::BS)) tet_stage_mfma(StageLaunch A) {
+__global__ void __launch_bounds__((MCfg<N, T>::BS), (MCfg<N, T>::WPE)) tet_stage_mfma(StageLaunch A) {
   using C = MCfg<N, T>;
   using Acc = typename MfmaAcc<T>::type;
   constexpr int NT = C::NT, NP = C::NP, EPB = C::EPB, BS = C::BS, FN = C::FN;
@@ -312,29 +322,27 @@ __global__ void __launch_bounds__((MCfg<N, T>::BS)) tet_stage_mfma(StageLaunch A
   __shared__ T sG[EPB * kTetGeoStride];
   __shared__ int sC[2][EPB * kTetConnStride];  // connectivity of this chunk and of the next one
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int lr = lane & 15, lk = lane >> 4;
+  const int lane = threadIdx.x & 63;
+  int tid = threadIdx.x, wave = tid >> 6, lr = lane & 15, lk = lane >> 4;
 
   // this wavefront's 16 operator rows as MFMA A operands, kept for the whole kernel
-  const T* __restrict__ gops = static_cast<const T*>(A.opsT);
-  const int orow = wave * 16 + lr;
+  // (laid out for it, 1 KB a load: read from the operators' rows a load touched
+  // 51 lines, 5 us of the 48 at N = 4 in FP32; hybrid stages of 68 784 elements
+  // at N = 4 129.6 -> 127.9 us, of 25 792 at N = 5 108 -> 99)
+  constexpr int SV = tet_frag_steps(N) / 4;
+  const V4<T>* __restrict__ gfrag =
+      reinterpret_cast<const V4<T>*>(static_cast<const T*>(A.opsT) + tet_row_ops(N)) + wave * SV * 64 + lane;
   T aD[3][C::KV], aL[C::KL];
 #pragma unroll
-  for (int o = 0; o < 3; ++o) {
+  for (int v = 0; v < SV; ++v) {
+    const V4<T> q = gfrag[v * 64];
+    const T qs[4] = {q.p, q.uz, q.ux, q.uy};
 #pragma unroll
-    for (int ks = 0; ks < C::KV; ++ks) {
-      const int col = 4 * ks + lk;
-      const bool ok = orow < NP && col < NP;
-      const T v = gops[ok ? o * NP * NP + orow * NP + col : 0];
-      aD[o][ks] = ok ? v : T(0);
+    for (int c = 0; c < 4; ++c) {
+      const int s = 4 * v + c;
+      if (s < 3 * C::KV) aD[s / C::KV][s % C::KV] = qs[c];
+      else if (s < 3 * C::KV + C::KL) aL[s - 3 * C::KV] = qs[c];
     }
-  }
-#pragma unroll
-  for (int ks = 0; ks < C::KL; ++ks) {
-    const int col = 4 * ks + lk;
-    const bool ok = orow < NP && col < FN;
-    const T v = gops[ok ? 3 * NP * NP + orow * FN + col : 0];
-    aL[ks] = ok ? v : T(0);
   }
 
   const V4<T>* __restrict__ Uin = static_cast<const V4<T>*>(A.Uin);
@@ -439,6 +447,7 @@ __global__ void __launch_bounds__((MCfg<N, T>::BS)) tet_stage_mfma(StageLaunch A
 
   int buf = 0;
   for (int64_t chunk = blockIdx.x; chunk < nchunks; chunk += gridDim.x, buf ^= 1) {
+    if constexpr (!C::HELD) asm volatile("" : "+v"(tid), "+v"(wave), "+v"(lr), "+v"(lk));
     const int64_t e0 = chunk * EPB;
     const int nE = int(A.Kt - e0 < EPB ? A.Kt - e0 : EPB);
     const int64_t next = chunk + gridDim.x;
