@@ -79,18 +79,18 @@ def table_stage_bytes(N: int, bits: int) -> int:
 
 def mortar_bytes(N: int, bits: int) -> int:
     """Algorithmic HBM bytes of one stage for one mortar face (a wedge
-    quadrilateral against two tetrahedron triangles): both packed coupling
-    matrices, the gathered face nodes ((N+1)^2 wedge + 2 Np_tri tetrahedron
+    quadrilateral against two tetrahedron triangles): three coupling
+    blocks (wedge-wedge of one side packed, wedge-tetrahedron of both), the gathered face nodes ((N+1)^2 wedge + 2 Np_tri tetrahedron
     4-vectors), the outputs (wedge pre-lift contributions [p, u][Nq][Np_tri
     padded to 4] and both tetrahedron-face fluxes [p, u][Np_tri]), the integer
-    record (8 int32) and the six FP64 geometry values the kernel reads."""
+    record (8 int32) and the eleven FP64 geometry values the kernel reads."""
     NT = (N + 1) * (N + 2) // 2
     Nq = N + 1
     ts = bits // 8
-    n = Nq * Nq + NT
-    core = (n * (n + 1) + 3) // 4 * 4
+    NW = Nq * Nq
+    core = (NW * (NW + 1) // 2 + 2 * NW * NT + 3) // 4 * 4
     ntp = (NT + 3) // 4 * 4
-    return core * ts + (Nq * Nq + 2 * NT) * 4 * ts + (2 * Nq * ntp + 4 * NT) * ts + 32 + 48
+    return core * ts + (Nq * Nq + 2 * NT) * 4 * ts + (2 * Nq * ntp + 4 * NT) * ts + 32 + 88
 
 
 TRAFFIC_FILE = os.path.join(os.path.dirname(os.path.abspath(__file__)), "profiles", "wedge_stage_cfg2_traffic.json")
