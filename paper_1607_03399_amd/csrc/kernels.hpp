@@ -208,9 +208,8 @@ hipError_t launch_batch_advance(int64_t* counter, hipStream_t st);
 // dJ/drho, and per face (bottom, top, quadrilaterals 0..2) the own side's
 // share of dJ/dZ, dt (dtau_p/dZ 1/2 int sig_p [p] + dtau_u/dZ 1/2 int sig_un
 // [u_n]) of the forward stage input Us (the penalties' derivatives are fixed
-// during the sweep).  kGradTerms: the partial sums behind them.
+// during the sweep).
 constexpr int kGradStride = 7;
-constexpr int kGradTerms = 12;
 template <typename T>
 constexpr int kGradRecord = sizeof(T) == 4 ? 2 * kGradStride : kGradStride;  // values per wedge
 // Gradient with respect to c and rho from the accumulated terms and the penalty

@@ -30,10 +30,16 @@ namespace {
 #ifndef WDG_W64
 #define WDG_W64 {0, 5, 4, 3, 2, 2}
 #endif
+#ifndef WDG_A32
+#define WDG_A32 {0, 8, 6, 5, 3, 2}
+#endif
+#ifndef WDG_A64
+#define WDG_A64 {0, 4, 4, 2, 1, 1}
+#endif
 template <int N, typename T, int MODE>
 constexpr int stage_waves() {
   constexpr int w32[6] = WDG_W32, w64[6] = WDG_W64;
-  constexpr int a32[6] = {0, 6, 4, 3, 2, 1}, a64[6] = {0, 4, 2, 1, 1, 1};  // adjoint
+  constexpr int a32[6] = WDG_A32, a64[6] = WDG_A64;  // adjoint
   if (MODE == 4) return sizeof(T) == 4 ? a32[N] : a64[N];
   return sizeof(T) == 4 ? w32[N] : w64[N];
 }
@@ -77,6 +83,16 @@ struct Cfg {
   // 4-vectors of the second region, the last one spare
   static constexpr int XV_ = EPB * (VLS + VGS) + (EPB * (XT + 2 * NQF) + 3) / 4;
   static constexpr int XV = (XV_ > PL ? XV_ : PL) + 1;
+  // the adjoint stage: a third set of planes, which later takes the jumps of
+  // its faces, behind the right-hand side's (over operators no longer needed)
+  static constexpr int JV = (EPB * (6 * Nq * Nq + 4 * NT) + 3) / 4;
+  static constexpr int XVG_ = PL + (JV > PL ? JV : PL);
+  static constexpr int XVG = XV > XVG_ ? XV : XVG_;
+  // Triangular faces: the first Nq / 2 lanes of an element share out the
+  // bottom's NT nodes, the others the top's, TPL each (surplus slots redo the
+  // last node).  NG: neighbour nodes a lane gathers.
+  static constexpr int TPL = (NT + Nq / 2 - 1) / (Nq / 2);
+  static constexpr int NG = Nq > TPL ? Nq : TPL;
 };
 
 // acc1 += c x1; acc2 += c x2 for a reference-operator entry c known at
@@ -192,71 +208,96 @@ __device__ __forceinline__ void grad_record_add(void* gacc, int64_t e, const Gra
 }
 
 // Gradient terms of one reverse stage of the adjoint sweep (MODE 4), run by
-// the stage kernel after its update.  The stage input (the adjoint stage
-// vector sig) is still staged in sU and the incoming adjoint state U~ in the
-// second region; the forward residual res_s after stage s, then the forward
-// stage input Us, are staged into them as they free up.  Per wedge it
-// accumulates the mass terms b_s U~_p^T M res_p, b_s U~_u^T M res_u (their sum
-// over a step's stages is that of dt sig_p^T M R_p, dt sig_u^T M R_u with R_s
-// the stage's right-hand side; as dJ/dc = 2/(c kappa) m_p, dJ/drho =
-// m_p/(rho kappa) + m_u) and per face dt times the face integrals 1/2 int
-// sig_p [p], 1/2 int sig_un [u_n] of Us weighted by the penalties'
-// derivatives (gacc slots 2..6), which the combine kernel adds up over both
-// sides of every face.  M^k = (sum_v w_v M_v) (x) M^1D and the face masses
-// are literals (reference triangle, 1D, edge masses).  The wavefronts share
-// the work as the stage does: each the mass term of its field; p, u_x, u_y
-// one quadrilateral face each, u_z the triangular faces.
-//
-// Loads of the epilogue, issued before the stage's last barriers: the chunk's
-// Us (a) and forward residual (b), coalesced, the neighbour nodes of Us on the
-// wavefront's face, the wedge's accumulators; and the geometry it uses, out
-// of the stage's LDS.
+// the stage kernel after its update.  Per wedge it accumulates the mass terms
+// b_s U~_p^T M res_p, b_s U~_u^T M res_u (their sum over a step's stages is
+// that of dt sig_p^T M R_p, dt sig_u^T M R_u with R_s the stage's right-hand
+// side; as dJ/dc = 2/(c kappa) m_p, dJ/drho = m_p/(rho kappa) + m_u) and per
+// face dt times the face integrals 1/2 int sig_p [p], 1/2 int sig_un [u_n] of
+// Us weighted by the penalties' derivatives (gacc slots 2..6), which the
+// combine kernel adds up over both sides of every face.  sig is the stage
+// input (the adjoint stage vector), U~ the incoming adjoint state, res_s the
+// forward residual after stage s, Us the forward stage input.
+// M^k = (sum_v w_v M_v) (x) M^1D and the face masses are literals (reference
+// triangle, 1D, edge masses).  The wavefronts share the work as the stage
+// does: each the mass term of its field; p, u_x, u_y one quadrilateral face
+// each, u_z the triangular faces, whose nodes and fields its lanes share out.
+// Bound by HBM and by the loads that the blocks of a CU keep in flight: sig
+// stays in LDS beside U~, a third set of planes (res_s, then the jumps of Us)
+// and the geometry values it reads; res_s and the gathers are loaded before
+// the update's stores, which a later load would wait for, and Us over the mass
+// terms, so that registers hold loads in flight only: at N = 3 in FP32 96 of
+// them and 32 KB, five blocks per CU.  us per reverse stage with sig, geometry
+// and all loads in registers (158, three blocks) and as it is: N = 3 in FP32 on
+// 524 288 wedges 560 -> 506 (4.3 TB/s), N = 5 on 73 728 592 -> 328, N = 3 in FP64
+// on 110 592 403 -> 290.
 template <int N, typename T>
 struct EpiData {
-  static constexpr int NT = Cfg<N, T>::NT, Nq = Cfg<N, T>::Nq;
-  V4<T> a[Cfg<N, T>::UPD], b[Cfg<N, T>::UPD];
-  int nbr, code; // across the wavefront's face (triangular: bottom for level 0, else top)
-  T fg[4];       // quadrilateral: J_f at its vertices, n_x, n_y; triangular (bottom for level 0, else top): J_f, n
-  T w0, w1, w2;  // weights of M^{tri,k}
+  using C = Cfg<N, T>;
+  V4<T> b[C::UPD];  // the chunk's res_s, coalesced
+  V4<T> gn[C::NG];  // neighbour nodes of Us on the lane's faces
+  bool inner;       // a neighbour across the lane's face
 };
+// what it reads of the geometry records: values kEpi0 .. kGeoStride - 1
+constexpr int kEpi0 = 9, kEpiStride = kGeoStride - kEpi0;
 template <int N, typename T>
 __device__ __forceinline__ void grad_load(const StageLaunch& A, int64_t e0, int nE, int tid, int f, int j, int64_t e,
-                                          int tnbr, int qnbr, int code, const T* g, EpiData<N, T>& L) {
+                                          int nbr, int code, const T* sG, T* sE, EpiData<N, T>& L) {
   using C = Cfg<N, T>;
-  constexpr int NT = C::NT, Nq = C::Nq, NP = C::NP, V4B = 4 * int(sizeof(T));
-  const V4<T>* __restrict__ Us = static_cast<const V4<T>*>(A.gUs);
+  constexpr int NT = C::NT, Nq = C::Nq, NP = C::NP, NG = C::NG, V4B = 4 * int(sizeof(T));
   const auto bb = chunk_rsrc(static_cast<const V4<T>*>(A.gRs) + e0 * NP, int64_t(nE) * NP * V4B);
-  const auto ba = chunk_rsrc(Us + e0 * NP, int64_t(nE) * NP * V4B);
 #pragma unroll
   for (int k = 0; k < C::UPD; ++k) L.b[k] = bload<T, kStream>(bb, tid + C::BS * k);
+  // the neighbour nodes of the stage's gathers (own element on the boundary):
+  // the branches choose the nodes, the loads are common
+  const int face = j < Nq / 2 ? 0 : 1, ti0 = (face ? j - Nq / 2 : j) * C::TPL;
+  const V4<T>* nb = static_cast<const V4<T>*>(A.gUs) + (nbr >= 0 ? int64_t(nbr) : e) * NP;
+  int off[NG];
+  if (f != 1) {
+    const int ned = (code >> (8 + 2 * (f == 0 ? 0 : f - 1))) & 3;
+    nb += j * NT;
 #pragma unroll
-  for (int k = 0; k < C::UPD; ++k) L.a[k] = bload<T>(ba, tid + C::BS * k);
-  const int gi = f != 1 ? 20 + 4 * (f == 0 ? 0 : f - 1) : 12 + 4 * (j == 0 ? 0 : 1);
+    for (int q = 0; q < NG; ++q)
+      off[q] = q >= Nq ? 0
+                       : (ned == 0 ? edge_node(N, 0, N - q) : (ned == 1 ? edge_node(N, 1, N - q) : edge_node(N, 2, N - q)));
+  } else {
+    const int pc = (code >> (3 * face)) & 7;
+    nb += (((code >> (6 + face)) & 1) ? N : 0) * NT;
 #pragma unroll
-  for (int k = 0; k < 4; ++k) L.fg[k] = g[gi + k];
-  L.nbr = f != 1 ? qnbr : tnbr;
-  L.code = code;
-  L.w0 = g[37];
-  L.w1 = g[38];
-  L.w2 = g[39];
+    for (int t = 0; t < NG; ++t) off[t] = face_perm<N>(pc, t < C::TPL && ti0 + t < NT ? ti0 + t : NT - 1);
+  }
+#pragma unroll
+  for (int t = 0; t < Nq; ++t) L.gn[t] = nb[off[t]];
+  if (f == 1) {
+#pragma unroll
+    for (int t = Nq; t < NG; ++t) L.gn[t] = nb[off[t]];
+  }
+  L.inner = nbr >= 0;
+  // the records' copy, before the right-hand side replaces them
+  for (int i = tid; i < C::EPB * kEpiStride; i += C::BS) {
+    const int el = i / kEpiStride;
+    sE[i] = sG[el * 4 * C::VGS + kEpi0 + i - el * kEpiStride];
+  }
 }
 
 template <int N, typename T>
 __device__ __forceinline__ void grad_epilogue(const StageLaunch& A, int tid, int f, int le, int j, bool active,
-                                              int64_t e, T* sU, T* sX, const EpiData<N, T>& L) {
+                                              int64_t e0, int nE, const T* sU, T* sX, T* sV, const T* sE,
+                                              const EpiData<N, T>& L) {
   using C = Cfg<N, T>;
   using RT = gen::RefTables<N>;
   constexpr int NT = C::NT, Nq = C::Nq, NP = C::NP, EPB = C::EPB, PL = C::PL;
   constexpr int GS = 3;  // partial sums per lane: mass term, face p, face u_n
-  static_assert(EPB * 3 * Nq * Nq * 2 <= 4 * PL, "jump scratch fits the state region");
   static_assert(4 * EPB * Nq * GS <= 4 * PL, "partial sums fit the second region");
   const T bsign = (A.flags & kDirichlet) ? T(-1) : T(1);
   const int ed = f == 0 ? 0 : f - 1;
   const int le0 = active ? le : 0;
   const int lb = le0 * NP + j * NT;  // the lane's level in a plane
-  auto slot = [&](int k) { return tid + C::BS * k < EPB * NP ? tid + C::BS * k : EPB * NP; };
+  const T* const g = sE + le0 * kEpiStride - kEpi0;  // the element's geometry record from kEpi0 on
+  // quadrilateral face: J_f at its vertices, n_x, n_y; triangular face (level j < Nq / 2: bottom): J_f, n
+  const int face = j < Nq / 2 ? 0 : 1, ti0 = (face ? j - Nq / 2 : j) * C::TPL;
+  const T* const fg = g + (f != 1 ? 20 + 4 * ed : 12 + 4 * face);
   auto put = [&](T* s, int k, const V4<T>& v) {
-    const int l = slot(k);
+    const int l = tid + C::BS * k < EPB * NP ? tid + C::BS * k : EPB * NP;
     s[l] = v.p;
     s[PL + l] = v.uz;
     s[2 * PL + l] = v.ux;
@@ -266,26 +307,15 @@ __device__ __forceinline__ void grad_epilogue(const StageLaunch& A, int tid, int
   auto qnode = [&](int q) {
     return lb + (ed == 0 ? edge_node(N, 0, q) : (ed == 1 ? edge_node(N, 1, q) : edge_node(N, 2, q)));
   };
-  // sig on the wavefront's face: (p, u_n)
-  T sp[NT], sn[NT];
-  if (f != 1) {
 #pragma unroll
-    for (int q = 0; q < Nq; ++q) {
-      const int i = qnode(q);
-      sp[q] = sU[i];
-      sn[q] = L.fg[2] * sU[2 * PL + i] + L.fg[3] * sU[3 * PL + i];
-    }
-  } else {
+  for (int k = 0; k < C::UPD; ++k) put(sV, k, L.b[k]);  // res_s
+  V4<T> a[C::UPD];  // the chunk's Us, in flight over the mass terms
+  {
+    const auto ba = chunk_rsrc(static_cast<const V4<T>*>(A.gUs) + e0 * NP, int64_t(nE) * NP * 4 * int(sizeof(T)));
 #pragma unroll
-    for (int i = 0; i < NT; ++i) {
-      sp[i] = sU[lb + i];
-      sn[i] = L.fg[1] * sU[2 * PL + lb + i] + L.fg[2] * sU[3 * PL + lb + i] + L.fg[3] * sU[PL + lb + i];
-    }
+    for (int k = 0; k < C::UPD; ++k) a[k] = bload<T>(ba, tid + C::BS * k);
   }
-  __syncthreads();  // the update and the reads of sig are done
-#pragma unroll
-  for (int k = 0; k < C::UPD; ++k) put(sU, k, L.b[k]);  // res_s over sig
-  __syncthreads();
+  __syncthreads();  // the update is done; U~, res_s complete
 
   // Mass terms.  The stage's right-hand side R_s enters as sig_s^T M R_s; with
   // dt R_s = res_s - a_s res_{s-1} (a_1 = 0) the sum over a step's stages equals
@@ -301,7 +331,8 @@ __device__ __forceinline__ void grad_epilogue(const StageLaunch& A, int tid, int
   }
   T mass = 0;
   {
-    const T* const rs = sU + f * PL + le0 * NP;
+    const T w0 = g[37], w1 = g[38], w2 = g[39];
+    const T* const rs = sV + f * PL + le0 * NP;
     const T* const ua = sX + f * PL + lb;
     T y[NT];
 #pragma unroll
@@ -322,9 +353,9 @@ __device__ __forceinline__ void grad_epilogue(const StageLaunch& A, int tid, int
 #pragma unroll
       for (int k = 0; k <= i; ++k) {
         T m = 0;
-        constexpr_or_skip(RT::Mv[i * NT + k], m, L.w0);
-        constexpr_or_skip(RT::Mv[NT * NT + i * NT + k], m, L.w1);
-        constexpr_or_skip(RT::Mv[2 * NT * NT + i * NT + k], m, L.w2);
+        constexpr_or_skip(RT::Mv[i * NT + k], m, w0);
+        constexpr_or_skip(RT::Mv[NT * NT + i * NT + k], m, w1);
+        constexpr_or_skip(RT::Mv[2 * NT * NT + i * NT + k], m, w2);
         z[i] += m * y[k];
         if (k < i) z[k] += m * y[i];
       }
@@ -332,59 +363,57 @@ __device__ __forceinline__ void grad_epilogue(const StageLaunch& A, int tid, int
 #pragma unroll
     for (int i = 0; i < NT; ++i) mass += ua[i] * z[i];
   }
-  // the neighbour nodes of Us on the wavefront's face, gathered here: held
-  // through the mass terms, their registers (40 at N = 3) cost a block per CU.
-  // The branches choose the nodes, the loads are common (see the stage).
-  const bool inner = L.nbr >= 0;
-  V4<T> gn[NT];
-  {
-    const V4<T>* __restrict__ Us = static_cast<const V4<T>*>(A.gUs);
-    const V4<T>* nb;
-    int off[NT];
-    if (f != 1) {
-      const int ned = (L.code >> (8 + 2 * ed)) & 3;
-      nb = Us + (inner ? int64_t(L.nbr) : e) * NP + j * NT;
-#pragma unroll
-      for (int q = 0; q < NT; ++q)
-        off[q] = q >= Nq ? 0
-                         : (ned == 0 ? edge_node(N, 0, N - q) : (ned == 1 ? edge_node(N, 1, N - q) : edge_node(N, 2, N - q)));
-    } else {
-      // lane 0 the bottom face, lane N the top one (own level); the other
-      // lanes, and boundary faces, read the own element: a valid address
-      // (one comparison for "level 0 or N": of (j == 0 || j == N) at N = 3 the
-      // compiler made a two-way switch that lost lane 0's neighbour)
-      const int tf = j == 0 ? 0 : 1;
-      const int pc = (L.code >> (3 * tf)) & 7;
-      const int nlev = ((L.code >> (6 + tf)) & 1) ? N : 0;
-      nb = Us + ((inner && j * (N - j) == 0) ? int64_t(L.nbr) : e) * NP + nlev * NT;
-#pragma unroll
-      for (int i = 0; i < NT; ++i) off[i] = face_perm<N>(pc, i);
-    }
-#pragma unroll
-    for (int i = 0; i < Nq; ++i) gn[i] = nb[off[i]];
-    if (f == 1) {
-#pragma unroll
-      for (int i = Nq; i < NT; ++i) gn[i] = nb[off[i]];
-    }
-  }
+  // (left alone, the sum moves below the barriers with its operands in registers)
+  asm volatile("" : "+v"(mass));
   __syncthreads();  // U~ and res_s in LDS are consumed
 #pragma unroll
-  for (int k = 0; k < C::UPD; ++k) put(sX, k, L.a[k]);  // Us
+  for (int k = 0; k < C::UPD; ++k) put(sX, k, a[k]);  // Us
   __syncthreads();
 
-  // faces: jumps of Us against the adjoint trace times the face mass
-  T fp = 0, fn = 0;
-  T ap[Nq], an[Nq];
+  // jumps of Us (over res_s): quadrilateral faces [edge][wedge][level][p, u_n][node],
+  // then triangular ones [wedge][face][p, u_n][node]; boundary faces see the mirror state
+  T* const sT = sV + EPB * 6 * Nq * Nq;
   if (f != 1) {
-    T jp[Nq], jn[Nq];
+    T* const o = sV + ((ed * EPB + le0) * Nq + j) * Nq * 2;
 #pragma unroll
     for (int q = 0; q < Nq; ++q) {
       const int i = qnode(q);
-      const T pm = sX[i], unm = L.fg[2] * sX[2 * PL + i] + L.fg[3] * sX[3 * PL + i];
-      const T pp = inner ? gn[q].p : bsign * pm;  // else the mirror state
-      const T unp = inner ? L.fg[2] * gn[q].ux + L.fg[3] * gn[q].uy : -bsign * unm;
-      jp[q] = pp - pm;
-      jn[q] = unp - unm;
+      const T pm = sX[i], unm = fg[2] * sX[2 * PL + i] + fg[3] * sX[3 * PL + i];
+      const T pp = L.inner ? L.gn[q].p : bsign * pm;
+      const T unp = L.inner ? fg[2] * L.gn[q].ux + fg[3] * L.gn[q].uy : -bsign * unm;
+      if (active) {
+        o[q] = pp - pm;
+        o[Nq + q] = unp - unm;
+      }
+    }
+  } else {
+    T* const o = sT + (le0 * 2 + face) * 2 * NT;
+#pragma unroll
+    for (int t = 0; t < C::TPL; ++t) {
+      const int i = ti0 + t < NT ? ti0 + t : NT - 1;
+      const int l = le0 * NP + face * N * NT + i;
+      const T pm = sX[l];
+      const T unm = fg[1] * sX[2 * PL + l] + fg[2] * sX[3 * PL + l] + fg[3] * sX[PL + l];
+      const T pp = L.inner ? L.gn[t].p : bsign * pm;
+      const T unp =
+          L.inner ? fg[1] * L.gn[t].ux + fg[2] * L.gn[t].uy + fg[3] * L.gn[t].uz : -bsign * unm;
+      if (active) {
+        o[i] = pp - pm;
+        o[NT + i] = unp - unm;
+      }
+    }
+  }
+  __syncthreads();  // jumps complete; Us in LDS is consumed
+
+  // against the trace of sig times the face mass
+  T fp = 0, fn = 0;
+  if (f != 1) {
+    T sp[Nq], sn[Nq], ap[Nq], an[Nq];
+#pragma unroll
+    for (int q = 0; q < Nq; ++q) {
+      const int i = qnode(q);
+      sp[q] = sU[i];
+      sn[q] = fg[2] * sU[2 * PL + i] + fg[3] * sU[3 * PL + i];
     }
 #pragma unroll
     for (int qq = 0; qq < Nq; ++qq) {
@@ -396,59 +425,11 @@ __device__ __forceinline__ void grad_epilogue(const StageLaunch& A, int tid, int
         constexpr_or_skip(RT::Mb[q * Nq + qq], vpb, sp[q]);
         constexpr_or_skip(RT::Mb[q * Nq + qq], vnb, sn[q]);
       }
-      ap[qq] = L.fg[0] * vpa + L.fg[1] * vpb;
-      an[qq] = L.fg[0] * vna + L.fg[1] * vnb;
+      ap[qq] = fg[0] * vpa + fg[1] * vpb;
+      an[qq] = fg[0] * vna + fg[1] * vnb;
     }
-    // the jumps to LDS [edge][wedge][level][p, u_n][node] (over res_s)
-    if (active) {
-      T* const o = sU + ((ed * EPB + le) * Nq + j) * Nq * 2;
-#pragma unroll
-      for (int q = 0; q < Nq; ++q) {
-        o[q] = jp[q];
-        o[Nq + q] = jn[q];
-      }
-    }
-  } else {
-    T jp[NT], jn[NT];
-#pragma unroll
-    for (int i = 0; i < NT; ++i) {
-      const T pm = sX[lb + i];
-      const T unm = L.fg[1] * sX[2 * PL + lb + i] + L.fg[2] * sX[3 * PL + lb + i] + L.fg[3] * sX[PL + lb + i];
-      const T pp = inner ? gn[i].p : bsign * pm;
-      const T unp = inner ? L.fg[1] * gn[i].ux + L.fg[2] * gn[i].uy + L.fg[3] * gn[i].uz : -bsign * unm;
-      jp[i] = pp - pm;
-      jn[i] = unp - unm;
-    }
-#pragma unroll
-    for (int i = 0; i < NT; ++i) {
-      T mp = 0, mn = 0;
-#pragma unroll
-      for (int k = 0; k < NT; ++k) {
-        constexpr_or_skip(RT::Mtri[i * NT + k], mp, jp[k]);
-        constexpr_or_skip(RT::Mtri[i * NT + k], mn, jn[k]);
-      }
-      fp += sp[i] * mp;
-      fn += sn[i] * mn;
-    }
-    fp *= T(0.5) * L.fg[0];
-    fn *= T(0.5) * L.fg[0];
-  }
-  // the wedge's accumulators, read before the level coupling
-  const bool last = f == 0 && active && j == 0;
-  GradRecord<T> rec;
-  T kap = 0, irho = 0, zsum[5];
-  if (last) {
-    grad_record_load<T>(A.gacc, e, rec);
-    const T* gm = static_cast<const T*>(A.geo) + e * kGeoStride;
-    kap = gm[9];
-    irho = gm[10];
-#pragma unroll
-    for (int k = 0; k < 5; ++k) zsum[k] = gm[32 + k];
-  }
-  __syncthreads();  // jumps complete; Us in LDS is consumed
-  if (f != 1) {
     // quadrilateral faces: couple the levels through M^1D
-    const T* const sj = sU + (ed * EPB + le0) * Nq * Nq * 2;
+    const T* const sj = sV + (ed * EPB + le0) * Nq * Nq * 2;
 #pragma unroll
     for (int m = 0; m < Nq; ++m) {
       T tp = 0, tn = 0;
@@ -462,7 +443,37 @@ __device__ __forceinline__ void grad_epilogue(const StageLaunch& A, int tid, int
     }
     fp *= T(0.5);
     fn *= T(0.5);
+  } else {
+    // sum_i sig_i sum_k Mtri[i][k] jump_k of one field; where a face has two
+    // lanes, the first takes p and the others u_n
+    auto contract = [&](bool un) {
+      const T* const jmp = sT + (le0 * 2 + face) * 2 * NT + (un ? NT : 0);
+      const T* const sg = sU + le0 * NP + face * N * NT;
+      T x[NT], s = 0;
+#pragma unroll
+      for (int k = 0; k < NT; ++k) x[k] = jmp[k];
+#pragma unroll
+      for (int i = 0; i < NT; ++i) {
+        T v = 0;
+#pragma unroll
+        for (int k = 0; k < NT; ++k) constexpr_or_skip(RT::Mtri[i * NT + k], v, x[k]);
+        const T t = un ? fg[1] * sg[2 * PL + i] + fg[2] * sg[3 * PL + i] + fg[3] * sg[PL + i] : sg[i];
+        s += t * v;
+      }
+      return s * (T(0.5) * fg[0]);
+    };
+    if constexpr (Nq / 2 > 1) {
+      fp = fn = contract(ti0 > 0);
+    } else {
+      fp = contract(false);
+      fn = contract(true);
+    }
   }
+  // the wedge's accumulators, read after the contractions (14 registers that
+  // would be held through them)
+  const bool last = f == 0 && active && j == 0;
+  GradRecord<T> rec;
+  if (last) grad_record_load<T>(A.gacc, e0 + le, rec);
   if (active) {
     T* const o = sX + ((f * EPB + le) * Nq + j) * GS;
     o[0] = mass;
@@ -478,10 +489,11 @@ __device__ __forceinline__ void grad_epilogue(const StageLaunch& A, int tid, int
       mp += part(0, l, 0);
       mu += part(1, l, 0) + part(2, l, 0) + part(3, l, 0);
     }
+    constexpr int top = Nq / 2, un = Nq / 2 > 1 ? 1 : 0;  // lanes of the top face; of u_n beside p
     tp[0] = part(1, 0, 1);
-    tn[0] = part(1, 0, 2);
-    tp[1] = part(1, N, 1);
-    tn[1] = part(1, N, 2);
+    tn[0] = part(1, un, 2);
+    tp[1] = part(1, top, 1);
+    tn[1] = part(1, top + un, 2);
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
       const int w = d == 0 ? 0 : d + 1;
@@ -492,6 +504,7 @@ __device__ __forceinline__ void grad_epilogue(const StageLaunch& A, int tid, int
         tn[2 + d] += part(w, l, 2);
       }
     }
+    const T kap = g[9], irho = g[10];
     const T c = std::sqrt(kap * irho);
     const T dt = T(A.dt);
     T x[kGradStride];
@@ -503,10 +516,10 @@ __device__ __forceinline__ void grad_epilogue(const StageLaunch& A, int tid, int
     const bool upwind = !(A.flags & kCentral);
 #pragma unroll
     for (int k = 0; k < 5; ++k) {
-      const T t = T(2) / zsum[k];
+      const T t = T(2) / g[32 + k];  // Z- + Z+
       x[2 + k] = upwind ? dt * (-T(0.5) * t * t * tp[k] - T(0.5) * tn[k]) : T(0);
     }
-    grad_record_add<T>(A.gacc, e, rec, x);
+    grad_record_add<T>(A.gacc, e0 + le, rec, x);
   }
 }
 
@@ -546,7 +559,8 @@ __device__ __forceinline__ void wedge_stage_chunk(const StageLaunch& A, int64_t 
   constexpr int VL = C::VL, VG = C::VG, VLS = C::VLS, GS = 4 * C::VGS, UPD = C::UPD;
   constexpr int V4B = 4 * int(sizeof(T));
   __shared__ T sU[4 * PL];  // planes p, u_z, u_x, u_y (the spare value of each takes the lanes past the chunk)
-  __shared__ V4<T> sX[C::XV];
+  __shared__ V4<T> sX[MODE == 4 ? C::XVG : C::XV];
+  [[maybe_unused]] __shared__ T sE[MODE == 4 ? EPB * kEpiStride : 1];
   V4<T>* const sL = sX;
   T* const sG = reinterpret_cast<T*>(sX + EPB * VLS);
   T* const sF = sG + EPB * GS;       // triangular-face fluxes [F_p, F_u][element][face][node]
@@ -570,9 +584,8 @@ __device__ __forceinline__ void wedge_stage_chunk(const StageLaunch& A, int64_t 
   const int64_t e = e0 + (active ? le : 0);  // idle lanes shadow a valid element
   const T bsign = (A.flags & kDirichlet) ? T(-1) : T(1);
   const T tau_on = (A.flags & kCentral) ? T(0) : T(1);
-  // Triangular faces: the first Nq / 2 lanes of an element share out the
-  // bottom's NT nodes, the others the top's (surplus slots redo the last node)
-  constexpr int per = (NT + Nq / 2 - 1) / (Nq / 2);
+  // triangular faces: see Cfg::TPL
+  constexpr int per = C::TPL;
   const int face = j < Nq / 2 ? 0 : 1;
   const int ti0 = (face ? j - Nq / 2 : j) * per;
 
@@ -611,7 +624,7 @@ __device__ __forceinline__ void wedge_stage_chunk(const StageLaunch& A, int64_t 
   // faces need beyond Nq.  (Loads of both branches into one array are merged
   // by the compiler component by component, and two arrays cost 16 registers
   // at N = 3: on 262 144 wedges 215 and 149 us per stage.)
-  constexpr int NG = Nq > per ? Nq : per;
+  constexpr int NG = C::NG;
   const V4<T>* nb;
   int off[NG];
   bool skip = false;  // layer marching: read from the staged chunk instead
@@ -1043,7 +1056,11 @@ __device__ __forceinline__ void wedge_stage_chunk(const StageLaunch& A, int64_t 
   // the gradient epilogue's loads and geometry, before the right-hand side
   // replaces the geometry records
   [[maybe_unused]] EpiData<N, T> ep;
-  if constexpr (MODE == 4) grad_load<N, T>(A, e0, nE, tid, f, j, e, j == 0 ? nb0 : nb1, qnbr, code, g, ep);
+  [[maybe_unused]] int eg = active ? le : 0;  // (the element anew, not held from the start: two registers)
+  if constexpr (MODE == 4) {
+    asm volatile("" : "+v"(eg));
+    grad_load<N, T>(A, e0, nE, tid, f, j, e0 + eg, f != 1 ? qnbr : tnbr, code, sG, sE, ep);
+  }
   // the right-hand side replaces factors, geometry and fluxes in LDS
   __syncthreads();
   if (active) {
@@ -1083,7 +1100,7 @@ __device__ __forceinline__ void wedge_stage_chunk(const StageLaunch& A, int64_t 
       else bstore<T, 0>(bout, idx, u);
     }
   }
-  if constexpr (MODE == 4) grad_epilogue<N, T>(A, tid, f, le, j, active, e, sU, sR, ep);
+  if constexpr (MODE == 4) grad_epilogue<N, T>(A, tid, f, le, j, active, e0, nE, sU, sR, sR + 4 * PL, sE, ep);
   if constexpr (MODE == 5) {
     __syncthreads();  // the update's reads of the staged state are done
     if (tid < NT) {
