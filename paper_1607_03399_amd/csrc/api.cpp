@@ -100,7 +100,7 @@ struct wdg_ctx {
   int cur = 0;
   void* dGeo = nullptr;
   void* dL = nullptr;   // (M^{tri,k})^-1, packed
-  void* dLn = nullptr;  // node-lane kernel (orders 4, 5 in FP32): L^{tri,k}
+  float* dLn = nullptr;  // L^{tri,k}, where the node-lane kernel runs (node_lift)
   void* dSrcVec = nullptr;
   double* dAux = nullptr;
   double* dMv = nullptr;
@@ -430,6 +430,21 @@ constexpr int64_t kNodeAutoWedges = 32;
 bool node_kernel(const wdg_ctx* ctx, int flags) {
   if (ctx->N < 4 || ctx->bits != 32 || (flags & (wdg::kLayerMarch | wdg::kGrad))) return false;
   return ctx->wedge_kernel == WDG_WEDGE_NODE || (ctx->wedge_kernel == WDG_WEDGE_AUTO && ctx->Kw < kNodeAutoWedges);
+}
+
+// L^{tri,k} of the mesh, built when the node-lane kernel first becomes this
+// context's (nothing else reads it: 912 bytes a wedge at order 4, 1776 at 5)
+int node_lift(wdg_ctx* ctx) {
+  if (ctx->dLn || ctx->Kw == 0) return WDG_OK;
+  const int NT = ctx->NT();
+  float* Ln = nullptr;
+  HIPCHK(hipMalloc(&Ln, size_t(ctx->Kw) * wdg::node_lift_stride(ctx->N) * sizeof(float)));
+  const hipError_t e =
+      wdg::launch_node_lift(ctx->N, ctx->Kw, ctx->dAux, ctx->dMv, ctx->dMv + 3 * NT * NT, Ln, ctx->stream);
+  if (e != hipSuccess) dfree(Ln);
+  HIPCHK(e);
+  ctx->dLn = Ln;
+  return WDG_OK;
 }
 
 // Cache policy of a stage over state buffers of state_bytes each (two states
@@ -1171,10 +1186,9 @@ int wdg_set_mesh(wdg_ctx* ctx, int64_t nv, const double* vxyz, int64_t nw, const
   HIPCHK(hipMalloc(&ctx->dRes, nstate));
   HIPCHK(hipMalloc(&ctx->dGeo, kw1 * wdg::kGeoStride * ts));
   HIPCHK(hipMalloc(&ctx->dL, kw1 * LS * ts));
-  if (ctx->N >= 4 && ctx->bits == 32) HIPCHK(hipMalloc(&ctx->dLn, kw1 * wdg::node_lift_stride(ctx->N) * ts));
   HIPCHK(hipMalloc(&ctx->dAux, kw1 * wdg::kAuxStride * sizeof(double)));
   HIPCHK(hipMalloc(&ctx->dConn, kw1 * wdg::kConnStride * sizeof(int32_t)));
-  HIPCHK(hipMalloc(&ctx->dMv, 3 * size_t(R.NT) * R.NT * sizeof(double)));
+  HIPCHK(hipMalloc(&ctx->dMv, 4 * size_t(R.NT) * R.NT * sizeof(double)));
   HIPCHK(hipMalloc(&ctx->dM1, size_t(R.Nq) * R.Nq * sizeof(double)));
   HIPCHK(hipMalloc(&ctx->dPartial, 2048 * sizeof(double)));
   HIPCHK(hipMalloc(&ctx->dSrcVec, size_t(wdg::kMaxSources) * R.NP * ts));
@@ -1183,26 +1197,27 @@ int wdg_set_mesh(wdg_ctx* ctx, int64_t nv, const double* vxyz, int64_t nw, const
   HIPCHK(hipMemsetAsync(ctx->dRes, 0, nstate, ctx->stream));
   HIPCHK(hipMemsetAsync(ctx->dSrcVec, 0, size_t(wdg::kMaxSources) * R.NP * ts, ctx->stream));
 
-  std::vector<double> Mv(3 * size_t(R.NT) * R.NT);
+  std::vector<double> Mv(4 * size_t(R.NT) * R.NT);
   for (int v = 0; v < 3; ++v) std::copy(R.Mv[v].begin(), R.Mv[v].end(), Mv.begin() + v * R.NT * R.NT);
+  std::copy(R.Mtri.begin(), R.Mtri.end(), Mv.begin() + 3 * R.NT * R.NT);
   HIPCHK(hipMemcpyAsync(ctx->dMv, Mv.data(), Mv.size() * sizeof(double), hipMemcpyHostToDevice, ctx->stream));
   {
     int rc = upload_vertical_mass(ctx);
     if (rc) return rc;
   }
   if (Kw > 0) {
-    double *dX = nullptr, *dMtri = nullptr;
+    double* dX = nullptr;
     HIPCHK(hipMalloc(&dX, ctx->X.size() * sizeof(double)));
-    HIPCHK(hipMalloc(&dMtri, R.Mtri.size() * sizeof(double)));
     HIPCHK(hipMemcpyAsync(dX, ctx->X.data(), ctx->X.size() * sizeof(double), hipMemcpyHostToDevice, ctx->stream));
-    HIPCHK(hipMemcpyAsync(dMtri, R.Mtri.data(), R.Mtri.size() * sizeof(double), hipMemcpyHostToDevice, ctx->stream));
     HIPCHK(hipMemcpyAsync(ctx->dConn, ctx->conn.data(), ctx->conn.size() * sizeof(int32_t), hipMemcpyHostToDevice,
                           ctx->stream));
-    HIPCHK(wdg::launch_setup(ctx->N, ctx->bits, Kw, dX, ctx->dMv, dMtri, ctx->dGeo, ctx->dL, ctx->dLn, ctx->dAux,
-                             ctx->stream));
+    HIPCHK(wdg::launch_setup(ctx->N, ctx->bits, Kw, dX, ctx->dMv, ctx->dGeo, ctx->dL, ctx->dAux, ctx->stream));
+    if (node_kernel(ctx, 0)) {
+      int rc = node_lift(ctx);
+      if (rc) return rc;
+    }
     HIPCHK(hipStreamSynchronize(ctx->stream));
     HIPCHK(hipFree(dX));
-    HIPCHK(hipFree(dMtri));
   }
   if (Kw > 0) {
     // column segments for marching: runs of consecutive wedges, each the top
@@ -1434,7 +1449,14 @@ int wdg_set_wedge_kernel(wdg_ctx* ctx, int variant) {
   if (!ctx) return WDG_ERR_ARG;
   if (variant != WDG_WEDGE_AUTO && variant != WDG_WEDGE_LEVEL && variant != WDG_WEDGE_NODE)
     return fail(ctx, WDG_ERR_ARG, "unknown wedge kernel");
+  const int was = ctx->wedge_kernel;
   ctx->wedge_kernel = variant;
+  if (!ctx->host_only && ctx->state >= kMesh && node_kernel(ctx, 0)) {
+    HIPCHK(hipSetDevice(ctx->device));
+    const int rc = node_lift(ctx);
+    if (rc) ctx->wedge_kernel = was;
+    return rc;
+  }
   return WDG_OK;
 }
 
@@ -2419,6 +2441,14 @@ int batch_upload_records(wdg_batch* b) {
     sb += state_bytes(q);
     rb += record_bytes(q);
   }
+  // a group keeps its kernel for the life of the batch, also where a problem's
+  // mesh or kernel was set again
+  for (const auto& g : b->groups)
+    for (int p : g.members)
+      if (g.node) {
+        if (const int rc = node_lift(b->probs[p])) return bfail(b, rc, b->probs[p]->err);
+        BHIPCHK(hipStreamSynchronize(b->probs[p]->stream));
+      }
   for (size_t i = 0; i < np; ++i) {
     wdg_ctx* ctx = b->probs[i];
     wdg::StageLaunch& A = L[i];

@@ -152,8 +152,11 @@ struct StageLaunch {
 int lift_stride(int N);
 int node_lift_stride(int N);
 
-hipError_t launch_setup(int N, int bits, int64_t K, const double* dX, const double* dMv, const double* dMtri,
-                        void* dGeo, void* dL, void* dLn, double* dAux, hipStream_t st);
+hipError_t launch_setup(int N, int bits, int64_t K, const double* dX, const double* dMv, void* dGeo, void* dL,
+                        double* dAux, hipStream_t st);
+// L^{tri,k} for the node-lane kernel (FP32) from the weights in dAux
+hipError_t launch_node_lift(int N, int64_t K, const double* dAux, const double* dMv, const double* dMtri, float* dLn,
+                            hipStream_t st);
 hipError_t launch_material(int bits, int64_t K, const double* dc, const double* drho, const int* dConn, void* dGeo,
                            double* dAux, hipStream_t st);
 // One stage: the mortar kernel (meshes with mortars), the wedge kernel, then

@@ -13,15 +13,42 @@ namespace {
 // ---------------------------------------------------------------------------
 constexpr int kMaxNT = 21;
 
+// By one wavefront, in LDS: Aug = [ M^{tri,k} | B ] to [ I | (M^{tri,k})^-1 B ],
+// M^{tri,k} = sum_v cw_v M_v, cw_v = J_tri h_v / 2, M_v = int l_a l_b lambda_v; B(r, c)
+// is any NT x NT matrix
+template <typename F>
+__device__ void solve_tri_mass(int NT, const double* cw, const double* __restrict__ Mv, F B, double* Aug, double* fac) {
+  const int tid = threadIdx.x, W = 2 * NT;
+  for (int idx = tid; idx < NT * W; idx += 64) {
+    const int r = idx / W, c = idx - r * W;
+    Aug[idx] = c < NT ? cw[0] * Mv[r * NT + c] + cw[1] * Mv[NT * NT + r * NT + c] + cw[2] * Mv[2 * NT * NT + r * NT + c]
+                      : B(r, c - NT);
+  }
+  __syncthreads();
+  // Gauss-Jordan elimination (M^{tri,k} is symmetric positive definite: no pivoting)
+  for (int p = 0; p < NT; ++p) {
+    const double piv = Aug[p * W + p];
+    __syncthreads();
+    for (int c = tid; c < W; c += 64) Aug[p * W + c] /= piv;
+    __syncthreads();
+    for (int r = tid; r < NT; r += 64) fac[r] = Aug[r * W + p];
+    __syncthreads();
+    for (int idx = tid; idx < NT * W; idx += 64) {
+      const int r = idx / W, c = idx - r * W;
+      if (r != p) Aug[idx] -= fac[r] * Aug[p * W + c];
+    }
+    __syncthreads();
+  }
+}
+
 template <typename T>
-__global__ void __launch_bounds__(64) setup_kernel(int NT, int LS, int LSN, int64_t K, const double* __restrict__ X,
-                                                   const double* __restrict__ Mv, const double* __restrict__ Mtri,
-                                                   T* __restrict__ geo, T* __restrict__ L, T* __restrict__ Ln,
-                                                   double* __restrict__ aux) {
-  __shared__ double Aug[kMaxNT * 3 * kMaxNT];
+__global__ void __launch_bounds__(64) setup_kernel(int NT, int LS, int64_t K, const double* __restrict__ X,
+                                                   const double* __restrict__ Mv, T* __restrict__ geo,
+                                                   T* __restrict__ L, double* __restrict__ aux) {
+  __shared__ double Aug[kMaxNT * 2 * kMaxNT];
   __shared__ double fac[kMaxNT];
   const int tid = threadIdx.x;
-  const int W = (Ln ? 3 : 2) * NT;
+  const int W = 2 * NT;
   for (int64_t k = blockIdx.x; k < K; k += gridDim.x) {
     const double* x = X + k * 18;
     double xb[3], yb[3], zb[3], zt[3];
@@ -91,34 +118,8 @@ __global__ void __launch_bounds__(64) setup_kernel(int NT, int LS, int LSN, int6
       ax[6] = 0.0;
       ax[7] = 0.0;
     }
-    // [ M^{tri,k} | I ] or, where L^{tri,k} is stored too, [ M^{tri,k} | I | M^tri ],
-    // M^{tri,k} = sum_v (J_tri h_v / 2) int l_a l_b lambda_v
-    for (int idx = tid; idx < NT * W; idx += 64) {
-      const int r = idx / W, c = idx - r * W;
-      double v;
-      if (c < NT) {
-        v = cw[0] * Mv[r * NT + c] + cw[1] * Mv[NT * NT + r * NT + c] + cw[2] * Mv[2 * NT * NT + r * NT + c];
-      } else {
-        v = c < 2 * NT ? ((c - NT == r) ? 1.0 : 0.0) : Mtri[r * NT + (c - 2 * NT)];
-      }
-      Aug[idx] = v;
-    }
-    __syncthreads();
-    // Gauss-Jordan elimination (M^{tri,k} is symmetric positive definite: no pivoting)
-    for (int p = 0; p < NT; ++p) {
-      const double piv = Aug[p * W + p];
-      __syncthreads();
-      for (int c = tid; c < W; c += 64) Aug[p * W + c] /= piv;
-      __syncthreads();
-      for (int r = tid; r < NT; r += 64) fac[r] = Aug[r * W + p];
-      __syncthreads();
-      for (int idx = tid; idx < NT * W; idx += 64) {
-        const int r = idx / W, c = idx - r * W;
-        if (r != p) Aug[idx] -= fac[r] * Aug[p * W + c];
-      }
-      __syncthreads();
-    }
-    // (M^{tri,k})^-1 is symmetric: its lower triangle, row by row; L^{tri,k} column by column
+    solve_tri_mass(NT, cw, Mv, [](int r, int c) { return r == c ? 1.0 : 0.0; }, Aug, fac);
+    // (M^{tri,k})^-1 is symmetric: its lower triangle, row by row
     for (int idx = tid; idx < LS; idx += 64) {
       double v = 0.0;
       if (idx < NT * (NT + 1) / 2) {
@@ -127,11 +128,24 @@ __global__ void __launch_bounds__(64) setup_kernel(int NT, int LS, int LSN, int6
       }
       L[k * LS + idx] = T(v);
     }
-    if (Ln) {
-      for (int idx = tid; idx < LSN; idx += 64) {
-        const int c = idx / NT, r = idx - c * NT;
-        Ln[k * LSN + idx] = T(idx < NT * NT ? Aug[r * W + 2 * NT + c] : 0.0);
-      }
+    __syncthreads();
+  }
+}
+
+// L^{tri,k} = (M^{tri,k})^-1 M^tri column by column (the node-lane stage kernel reads it)
+__global__ void __launch_bounds__(64) node_lift_kernel(int NT, int LSN, int64_t K, const double* __restrict__ aux,
+                                                       const double* __restrict__ Mv, const double* __restrict__ Mtri,
+                                                       float* __restrict__ Ln) {
+  __shared__ double Aug[kMaxNT * 2 * kMaxNT];
+  __shared__ double fac[kMaxNT];
+  const int W = 2 * NT;
+  for (int64_t k = blockIdx.x; k < K; k += gridDim.x) {
+    const double* ax = aux + k * kAuxStride;
+    const double cw[3] = {ax[0], ax[1], ax[2]};
+    solve_tri_mass(NT, cw, Mv, [&](int r, int c) { return Mtri[r * NT + c]; }, Aug, fac);
+    for (int idx = threadIdx.x; idx < LSN; idx += 64) {
+      const int c = idx / NT, r = idx - c * NT;
+      Ln[k * LSN + idx] = float(idx < NT * NT ? Aug[r * W + NT + c] : 0.0);
     }
     __syncthreads();
   }
@@ -281,19 +295,28 @@ int node_lift_stride(int N) {
   return (NT * NT + 3) / 4 * 4;
 }
 
-hipError_t launch_setup(int N, int bits, int64_t K, const double* dX, const double* dMv, const double* dMtri,
-                        void* dGeo, void* dL, void* dLn, double* dAux, hipStream_t st) {
-  if (dLn && !dMtri) return hipErrorInvalidValue;
+hipError_t launch_setup(int N, int bits, int64_t K, const double* dX, const double* dMv, void* dGeo, void* dL,
+                        double* dAux, hipStream_t st) {
   const int NT = (N + 1) * (N + 2) / 2;
-  const int LS = lift_stride(N), LSN = node_lift_stride(N);
+  const int LS = lift_stride(N);
   int64_t nb = K < 65536 ? K : 65536;
   if (nb <= 0) return hipSuccess;
   if (bits == 32)
-    hipLaunchKernelGGL(setup_kernel<float>, dim3(unsigned(nb)), dim3(64), 0, st, NT, LS, LSN, K, dX, dMv, dMtri,
-                       static_cast<float*>(dGeo), static_cast<float*>(dL), static_cast<float*>(dLn), dAux);
+    hipLaunchKernelGGL(setup_kernel<float>, dim3(unsigned(nb)), dim3(64), 0, st, NT, LS, K, dX, dMv,
+                       static_cast<float*>(dGeo), static_cast<float*>(dL), dAux);
   else
-    hipLaunchKernelGGL(setup_kernel<double>, dim3(unsigned(nb)), dim3(64), 0, st, NT, LS, LSN, K, dX, dMv, dMtri,
-                       static_cast<double*>(dGeo), static_cast<double*>(dL), static_cast<double*>(dLn), dAux);
+    hipLaunchKernelGGL(setup_kernel<double>, dim3(unsigned(nb)), dim3(64), 0, st, NT, LS, K, dX, dMv,
+                       static_cast<double*>(dGeo), static_cast<double*>(dL), dAux);
+  return hipGetLastError();
+}
+
+hipError_t launch_node_lift(int N, int64_t K, const double* dAux, const double* dMv, const double* dMtri, float* dLn,
+                            hipStream_t st) {
+  const int NT = (N + 1) * (N + 2) / 2;
+  int64_t nb = K < 65536 ? K : 65536;
+  if (nb <= 0) return hipSuccess;
+  hipLaunchKernelGGL(node_lift_kernel, dim3(unsigned(nb)), dim3(64), 0, st, NT, node_lift_stride(N), K, dAux, dMv, dMtri,
+                     dLn);
   return hipGetLastError();
 }
 
