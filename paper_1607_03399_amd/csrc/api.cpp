@@ -2281,10 +2281,15 @@ int wdg_get_element_data(const wdg_ctx* ctx, double* geo, double* lift) {
     int rc = fetch(ctx->dL, size_t(ctx->Kw) * LS, pk.data(), LS, NPK);
     if (rc) return rc;
     const RefOps& R = *ctx->ref;
-    std::vector<double> Mi(size_t(NT) * NT);
+    std::vector<double> Mi(size_t(NT) * NT), g(size_t(ctx->Kw) * wdg::kGeoStride);
+    rc = fetch(ctx->dGeo, g.size(), g.data(), wdg::kGeoStride, wdg::kGeoStride);
+    if (rc) return rc;
     for (int64_t k = 0; k < ctx->Kw; ++k) {
+      const bool tiny = ctx->bits == 32 && g[size_t(k) * wdg::kGeoStride + 37] < double(wdg::kTinyWeight);
+      const double unit = tiny ? double(wdg::kTinyUp) : 1.0;
       for (int r = 0; r < NT; ++r)
-        for (int c = 0; c <= r; ++c) Mi[r * NT + c] = Mi[c * NT + r] = pk[size_t(k) * NPK + r * (r + 1) / 2 + c];
+        for (int c = 0; c <= r; ++c)
+          Mi[r * NT + c] = Mi[c * NT + r] = unit * pk[size_t(k) * NPK + r * (r + 1) / 2 + c];
       for (int r = 0; r < NT; ++r)
         for (int c = 0; c < NT; ++c) {
           double v = 0.0;

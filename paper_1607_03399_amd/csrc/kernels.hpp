@@ -144,6 +144,13 @@ struct StageLaunch {
   int ncols;
 };
 
+// FP32 elements whose first mass weight J_tri h_v / 2 (of the geometry record)
+// is below this: entries of M^{tri,k} are denormal numbers there, those of its
+// inverse overflow.  The inverse is stored times this number, and what it
+// is applied to multiplied by the reciprocal (exact: a power of two).
+constexpr float kTinyWeight = 0x1p-96f;
+constexpr float kTinyUp = 0x1p96f;
+
 // Per-element stride (values, a multiple of 4) of the lower triangle of
 // (M^{tri,k})^-1, row by row (the level-lane stage kernels read it at the
 // orders whose mass they do not factor themselves), and of the lift

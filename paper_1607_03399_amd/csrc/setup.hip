@@ -120,13 +120,14 @@ __global__ void __launch_bounds__(64) setup_kernel(int NT, int LS, int64_t K, co
     }
     solve_tri_mass(NT, cw, Mv, [](int r, int c) { return r == c ? 1.0 : 0.0; }, Aug, fac);
     // (M^{tri,k})^-1 is symmetric: its lower triangle, row by row
+    const double unit = sizeof(T) == 4 && T(cw[0]) < T(kTinyWeight) ? double(kTinyWeight) : 1.0;
     for (int idx = tid; idx < LS; idx += 64) {
       double v = 0.0;
       if (idx < NT * (NT + 1) / 2) {
         const int r = tri_row(idx), c = idx - r * (r + 1) / 2;
         v = 0.5 * (Aug[r * W + NT + c] + Aug[c * W + NT + r]);
       }
-      L[k * LS + idx] = T(v);
+      L[k * LS + idx] = T(v * unit);
     }
     __syncthreads();
   }

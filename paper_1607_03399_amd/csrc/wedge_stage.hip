@@ -153,8 +153,15 @@ __device__ __forceinline__ T dot3(T a, T x, T b, T y, T c, T z) {
   return std::fma(c, z, dot2(a, x, b, y));
 }
 
-// 1 / x and 1 / sqrt(x) of positive normal numbers to about one unit in the
-// last place: the hardware approximation refined by Newton steps (in place of
+// elements whose mass is scaled before it is factored or inverted (kTinyWeight)
+template <typename T>
+__device__ __forceinline__ bool tiny(T w0) {
+  return sizeof(T) == 4 && w0 < T(kTinyWeight);
+}
+
+// 1 / x and 1 / sqrt(x) of positive normal numbers (sums of impedances, whose
+// reciprocals the records hold as normal numbers too; a factor's pivots, see
+// tiny) to about one unit in the last place: the hardware approximation refined by Newton steps (in place of
 // the division and square root sequences, which also cover the special
 // values: 250 of the 604 instructions of the factor below at N = 3)
 __device__ __forceinline__ float inv(float x) {
@@ -780,7 +787,14 @@ __device__ __forceinline__ void wedge_stage_chunk(const StageLaunch& A, int64_t 
       // slots (entry (i, m) at i (i + 1) / 2 + m, the diagonal holding 1 / L_ii)
       if (active && j == 0) {
         constexpr int NK = Dim<N>::NPK;
-        const T w0 = g[37], w1 = g[38], w2 = g[39];
+        T w0 = g[37], w1 = g[38], w2 = g[39];
+        const bool small = tiny(w0);
+        if (__builtin_amdgcn_ballot_w64(small)) {
+          const T up = small ? T(kTinyUp) : T(1);
+          w0 *= up;
+          w1 *= up;
+          w2 *= up;
+        }
         T a[4 * VL];
 #pragma unroll
         for (int q = 0; q < NK; ++q) {
@@ -798,6 +812,12 @@ __device__ __forceinline__ void wedge_stage_chunk(const StageLaunch& A, int64_t 
 #pragma unroll
           for (int k = 0; k < m; ++k) sm -= a[i * (i + 1) / 2 + k] * a[m * (m + 1) / 2 + k];
           a[q] = m < i ? sm * a[m * (m + 1) / 2 + m] : inv_sqrt(sm);
+        }
+        if (__builtin_amdgcn_ballot_w64(small)) {
+          // the factor itself: 2^96 = (2^48)^2
+          const T d = small ? T(0x1p48) : T(1), o = small ? T(0x1p-48) : T(1);
+#pragma unroll
+          for (int q = 0; q < NK; ++q) a[q] *= q == tri_row(q) * (tri_row(q) + 3) / 2 ? d : o;
         }
 #pragma unroll
         for (int q = NK; q < 4 * VL; ++q) a[q] = T(0);
@@ -989,6 +1009,12 @@ __device__ __forceinline__ void wedge_stage_chunk(const StageLaunch& A, int64_t 
       for (int i = 0; i < NT; ++i) {
         B[i] = R[i];
         R[i] = T(0);
+      }
+      const bool small = tiny(g[37]);
+      if (__builtin_amdgcn_ballot_w64(small)) {
+        const T up = small ? T(kTinyUp) : T(1);
+#pragma unroll
+        for (int i = 0; i < NT; ++i) B[i] *= up;
       }
 #pragma unroll
       for (int c = 0; c < VL; ++c) {
