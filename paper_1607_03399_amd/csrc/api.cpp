@@ -447,14 +447,19 @@ int node_lift(wdg_ctx* ctx) {
   return WDG_OK;
 }
 
-// Cache policy of a stage over state buffers of state_bytes each (two states
-// and the residual) and record_bytes of element records.  What fits the 256
-// MiB Infinity Cache is left to it, the rest streams past the caches: nothing,
-// the residual, or residual and output state.  us per stage, nothing / residual
-// / both streamed: order 3 FP32, 106 496 wedges (215 MiB in all) 51 / - / 63;
-// 122 880 (248 MiB; without the residual 173) 77 / 64 / 71; 155 648 (219 without)
-// 99 / 77 / 88; 188 416 (265 without) 117 / 120 / 105; order 1, 1 048 576 wedges
-// (384 without) - / 117 / 110.
+// Cache policy of the wedge kernel's residual and output state in a stage over
+// state buffers of state_bytes each (two states and the residual) and
+// record_bytes of element records (the tetrahedron, mortar and node-lane kernels
+// always stream what they write).  What fits the 256 MiB Infinity Cache is
+// left to it, the rest streams past the caches: nothing, the residual, or
+// residual and output state.  us per stage, nothing / residual / both streamed:
+// order 3 FP32, 106 496 wedges (215 MiB in all) 51 / - / 63; 122 880 (248 MiB;
+// without the residual 173) 77 / 64 / 71; 155 648 (219 without) 99 / 77 / 88;
+// 188 416 (265 without) 117 / 120 / 105; order 1, 1 048 576 wedges (384
+// without) - / 117 / 110; order 4, 54 400 (222 MiB) 57 / 59 / 64, 60 800 (248)
+// 70 / 65 / 71; order 5, 32 768 (224 MiB) 68 / 70 / 74, 40 960 (280) 91 / 85 / 89.
+// A mortar's blocks do not count: they stream (hybrid mesh of 39 312 wedges and
+// 29 520 tetrahedra at order 4, 213 MiB without them and 344 with: 129 / 130 / 134).
 int stream_flags(size_t state_bytes, size_t record_bytes) {
   const size_t MiB = size_t(1) << 20;
   return (3 * state_bytes + record_bytes > 232 * MiB ? wdg::kStreamRes : 0) |
@@ -462,7 +467,9 @@ int stream_flags(size_t state_bytes, size_t record_bytes) {
 }
 size_t state_bytes(const wdg_ctx* ctx) { return size_t(ctx->nodes()) * 4 * ctx->tsize(); }
 size_t record_bytes(const wdg_ctx* ctx) {
-  return size_t(ctx->Kw) * (wdg::kGeoStride * ctx->tsize() + wdg::kConnStride * sizeof(int)) +
+  // (the packed inverse mass is read from order 4 on, whose mass is not factored in the kernel)
+  const size_t inverse = ctx->N >= 4 ? size_t(wdg::lift_stride(ctx->N)) : 0;
+  return size_t(ctx->Kw) * ((wdg::kGeoStride + inverse) * ctx->tsize() + wdg::kConnStride * sizeof(int)) +
          size_t(ctx->Kt) * (wdg::kTetGeoStride * ctx->tsize() + wdg::kTetConnStride * sizeof(int));
 }
 
