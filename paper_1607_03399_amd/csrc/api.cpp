@@ -473,6 +473,19 @@ size_t record_bytes(const wdg_ctx* ctx) {
          size_t(ctx->Kt) * (wdg::kTetGeoStride * ctx->tsize() + wdg::kTetConnStride * sizeof(int));
 }
 
+// The same for a stage with these flags.  The adjoint's forward stages write
+// state and residual out of place (kResOut), four buffers in all; they are
+// read again by the next stage, and by the reverse sweep when the caches have
+// long moved on.  us per stage of a gradient, both always streamed and by this
+// rule: order 3 FP32 on 73 728 wedges (202 MiB) 152 -> 148, order 3 FP64 on
+// 24 576 126 -> 118, order 1 FP64 on 147 456 137 -> 128; above the line, order 3 on
+// 98 304 (270 MiB), streamed 194, not 199.
+int stage_stream_flags(const wdg_ctx* ctx, int flags) {
+  const size_t sb = state_bytes(ctx), rb = record_bytes(ctx);
+  if (flags & wdg::kResOut) return 4 * sb + rb > (size_t(232) << 20) ? wdg::kStreamRes | wdg::kStreamU : 0;
+  return stream_flags(sb, rb);
+}
+
 hipError_t launch_wedges(const wdg_ctx* ctx, const wdg::StageLaunch& L) {
   if (node_kernel(ctx, L.flags))
     return wdg::launch_wedge_node_stage(ctx->N, ctx->bits,
@@ -524,10 +537,7 @@ int launch_stage(wdg_ctx* ctx, const void* Uin, void* Uout, void* res, double a,
   L.tet_blocks = ctx->tet_blocks;
   L.cols = ctx->dCols;
   L.ncols = ctx->ncols;
-  // (the adjoint's forward and reverse stages walk through many states)
-  const int stream = (flags & (wdg::kResOut | wdg::kGrad)) ? wdg::kStreamRes | wdg::kStreamU
-                                                           : stream_flags(state_bytes(ctx), record_bytes(ctx));
-  L.flags = flags | stream | (g != 1.0 ? wdg::kGamma : 0) | (ctx->layer_march != WDG_MARCH_OFF ? wdg::kLayerMarch : 0) |
+  L.flags = flags | stage_stream_flags(ctx, flags) | (g != 1.0 ? wdg::kGamma : 0) | (ctx->layer_march != WDG_MARCH_OFF ? wdg::kLayerMarch : 0) |
             (ctx->layer_march == WDG_MARCH_COLUMN ? wdg::kColumnMarch : 0) | (ctx->tet_valu ? wdg::kTetValu : 0) | (ctx->bc == WDG_BC_DIRICHLET_P0 ? wdg::kDirichlet : 0) |
             (ctx->flux == WDG_FLUX_CENTRAL ? wdg::kCentral : 0) | (ctx->mass == WDG_MASS_LUMPED ? wdg::kLumped : 0);
   if (ctx->timing) {

@@ -48,3 +48,26 @@ def test_streamed_and_cached_stages_agree():
     s.close()
     assert all(np.array_equal(a, small_out[0]) for a in small_out[1:])
     assert all(np.array_equal(a, big_out[0]) for a in big_out[1:])
+
+
+def test_streamed_and_cached_gradients_agree():
+    """250 wedges alone (nothing streams) and in front of 425 984 others that
+    touch none of them (234 MiB in the adjoint's forward stages: their outputs
+    stream): the gradient of receivers in the 250 is the same bit for bit."""
+    m = inputs.layered_config(5, 5, 0.3, seed=3)
+    far = inputs.layered_config(64, 52, 0.3, seed=2)
+    both = inputs.WedgeMesh(np.concatenate([m.verts, far.verts + [10.0, 0.0, 0.0]]),
+                            np.concatenate([m.wedges, far.wedges + len(m.verts)]), np.concatenate([m.c, far.c]),
+                            np.concatenate([m.rho, far.rho]), m.layers, "both")
+    rec = np.random.default_rng(0).uniform(0.2, 0.8, (8, 3))
+    w = np.random.default_rng(1).standard_normal((4, 8))
+    out = []
+    for mesh in (m, both):
+        s = _solver(mesh, 1, 32)
+        s.set_receivers(rec)
+        out.append(s.adjoint_gradient(4, 1e-3, w, checkpoint_every=3))
+        s.close()
+    for alone, beside in zip(*out):
+        assert np.abs(alone).max() > 0
+        assert np.array_equal(alone, beside[:len(alone)])
+        assert not beside[len(alone):].any()
