@@ -660,11 +660,14 @@ std::vector<double> mortar_tables(const RefOps& R) {
 // face's Lagrange basis) and dA the physical area element of the wedge face.
 // The side is integrated in the wedge face's (xi, t) coordinates: mort_nx(N)
 // Gauss points in xi times Nq Gauss points in t between the bottom (top) and
-// the diagonal, exact in t at fixed xi (degree <= 2N); lower triangles packed
-// by columns, both sides per mortar, wdg::mort_core_stride values each.
-std::vector<double> mortar_cores(const RefOps& R, const std::vector<MortarHost>& mort) {
+// the diagonal, exact in t at fixed xi (degree <= 2N).  store(m, C) takes mortar
+// m's lower triangles packed by columns, both sides (on worker threads, each
+// mortar once); without all, of the wedge-wedge blocks only side 0's and no
+// tetrahedron-tetrahedron block are integrated (the rest of C is undefined).
+template <typename F>
+void mortar_integrals(const RefOps& R, const std::vector<MortarHost>& mort, bool all, F store) {
   const int N = R.N, NT = R.NT, Nq = R.Nq, NW = Nq * Nq, n = wdg::mort_core_n(N), NX = wdg::mort_nx(N);
-  const int CS = wdg::mort_core_stride(N), NPK = n * (n + 1) / 2;
+  const int NPK = n * (n + 1) / 2;
   std::vector<double> xg, wg, tg, wt;
   wdg::gauss_legendre(NX, xg, wg);
   wdg::gauss_legendre(Nq, tg, wt);
@@ -683,13 +686,13 @@ std::vector<double> mortar_cores(const RefOps& R, const std::vector<MortarHost>&
   std::vector<double> lxi(size_t(NX) * Nq);
   for (int a = 0; a < NX; ++a) R.line_basis(xg[a], &lxi[size_t(a) * Nq]);
   const size_t nm = mort.size();
-  std::vector<double> out(nm * CS, 0.0);
   auto work = [&](size_t m0, size_t m1) {
-    std::vector<double> b(n), lt(Nq), pr(N + 1), ps(N + 1), ph(NT);
+    std::vector<double> b(n), lt(Nq), pr(N + 1), ps(N + 1), ph(NT), both(2 * size_t(NPK));
     for (size_t m = m0; m < m1; ++m) {
       const MortarHost& M = mort[m];
+      std::fill(both.begin(), both.end(), 0.0);
       for (int side = 0; side < 2; ++side) {
-        double* C = &out[m * CS + size_t(side) * NPK];
+        double* C = &both[size_t(side) * NPK];
         const double* lm = M.lam[side];
         for (int a = 0; a < NX; ++a) {
           const double xi = xg[a];
@@ -718,14 +721,15 @@ std::vector<double> mortar_cores(const RefOps& R, const std::vector<MortarHost>&
               for (int k = 0; k < NT; ++k) v += Vinv[k * NT + i] * ph[k];
               b[NW + i] = v;
             }
-            int o = 0;
-            for (int c = 0; c < n; ++c) {
+            for (int c = 0; c < (all ? n : NW); ++c) {
               const double wc = w * b[c];
-              for (int r = c; r < n; ++r) C[o++] += wc * b[r];
+              double* col = C + c * n - c * (c - 1) / 2 - c;  // entry (c, r) at col[r]
+              for (int r = all || side == 0 ? c : NW; r < n; ++r) col[r] += wc * b[r];
             }
           }
         }
       }
+      store(m, both.data());
     }
   };
   const size_t nthr = std::min<size_t>(std::max(1u, std::thread::hardware_concurrency()), 16);
@@ -740,24 +744,31 @@ std::vector<double> mortar_cores(const RefOps& R, const std::vector<MortarHost>&
     }
     for (auto& th : pool) th.join();
   }
+}
+
+// Whole coupling matrices, wdg::mort_core_stride values each
+std::vector<double> mortar_cores(const RefOps& R, const std::vector<MortarHost>& mort) {
+  const size_t CS = wdg::mort_core_stride(R.N), used = size_t(wdg::mort_core_n(R.N)) * (wdg::mort_core_n(R.N) + 1);
+  std::vector<double> out(mort.size() * CS, 0.0);
+  mortar_integrals(R, mort, true, [&](size_t m, const double* C) { std::copy(C, C + used, &out[m * CS]); });
   return out;
 }
 
-// The blocks of mortar_cores that the device keeps (wdg::mort_dev_stride)
-std::vector<double> mortar_blocks(int N, const std::vector<double>& cores) {
-  const int NT = (N + 1) * (N + 2) / 2, NW = (N + 1) * (N + 1), n = wdg::mort_core_n(N), NPK = n * (n + 1) / 2;
-  const size_t CS = wdg::mort_core_stride(N), DS = wdg::mort_dev_stride(N), nm = cores.size() / CS;
-  std::vector<double> out(nm * DS, 0.0);
-  for (size_t m = 0; m < nm; ++m) {
-    const double* C = &cores[m * CS];
-    double* o = &out[m * DS];
+// The blocks that the device keeps (wdg::mort_dev_stride), in its precision
+template <typename T>
+std::vector<unsigned char> mortar_blocks(const RefOps& R, const std::vector<MortarHost>& mort) {
+  const int NT = R.NT, NW = R.Nq * R.Nq, n = wdg::mort_core_n(R.N), NPK = n * (n + 1) / 2;
+  const size_t DS = wdg::mort_dev_stride(R.N);
+  std::vector<unsigned char> out(mort.size() * DS * sizeof(T), 0);
+  mortar_integrals(R, mort, false, [&](size_t m, const double* C) {
+    T* o = reinterpret_cast<T*>(out.data()) + m * DS;
     auto at = [n](int c, int r) { return c * n - c * (c - 1) / 2 + r - c; };
     for (int c = 0; c < NW; ++c)
-      for (int r = c; r < NW; ++r) *o++ = C[at(c, r)];
+      for (int r = c; r < NW; ++r) *o++ = T(C[at(c, r)]);
     for (int side = 0; side < 2; ++side)
       for (int i = 0; i < NT; ++i)
-        for (int c = 0; c < NW; ++c) *o++ = C[size_t(side) * NPK + at(c, NW + i)];
-  }
+        for (int c = 0; c < NW; ++c) *o++ = T(C[side * NPK + at(c, NW + i)]);
+  });
   return out;
 }
 
@@ -1336,7 +1347,8 @@ int wdg_set_mesh(wdg_ctx* ctx, int64_t nv, const double* vxyz, int64_t nw, const
     const std::vector<double> tabs = mortar_tables(R);
     if (int(tabs.size()) != wdg::mortar_table_size(ctx->N)) return fail(ctx, WDG_ERR_HIP, "mortar table layout");
     const std::vector<unsigned char> tabT = to_precision(tabs, ctx->bits);
-    const std::vector<unsigned char> cores = to_precision(mortar_blocks(ctx->N, mortar_cores(R, ctx->mort)), ctx->bits);
+    const std::vector<unsigned char> cores =
+        ctx->bits == 32 ? mortar_blocks<float>(R, ctx->mort) : mortar_blocks<double>(R, ctx->mort);
     HIPCHK(hipMalloc(&ctx->dMortI, mi.size() * sizeof(int32_t)));
     HIPCHK(hipMalloc(&ctx->dMortG, nm * wdg::kMortGeoStride * sizeof(double)));
     HIPCHK(hipMalloc(&ctx->dMortTab, tabT.size()));
