@@ -163,7 +163,10 @@ int wdg_set_tet_kernel(wdg_ctx* ctx, int variant);
  * WDG_WEDGE_AUTO (default): level-lane, but for meshes of fewer than 32
  * wedges node-lane wherever it exists.
  * WDG_WEDGE_LEVEL: level-lane everywhere.  WDG_WEDGE_NODE: node-lane
- * wherever it exists.  Other values: WDG_ERR_ARG. */
+ * wherever it exists.  Other values: WDG_ERR_ARG.  A choice (or a mesh set
+ * later) that brings the node-lane kernel in builds its operator, 912 (order 4)
+ * or 1776 (order 5) bytes a wedge of device memory: WDG_ERR_OOM where that does
+ * not fit, the former choice then stays. */
 enum { WDG_WEDGE_AUTO = 0, WDG_WEDGE_LEVEL = 1, WDG_WEDGE_NODE = 2 };
 int wdg_set_wedge_kernel(wdg_ctx* ctx, int variant);
 
@@ -319,7 +322,8 @@ int wdg_set_adjoint_memory_limit(wdg_ctx* ctx, int64_t bytes);
  *     registers) -- on the real data, as the median of five
  *     launches that rewrite only the residual (which the next stage
  *     overwrites anyway), and keeps the fastest; without autotuning the first
- *     candidate (the single-problem kernel's shape).  Then it captures the
+ *     candidate (the single-problem kernel's shape).  An order with problems on
+ *     both kernels and few chunks is one group, of one shape.  Then it captures the
  *     step graph.  No problem may be added afterwards (WDG_ERR_STATE).
  *   wdg_batch_step: nsteps steps of every problem from its current fields and
  *     time (each with its own time step); afterwards wdg_get_fields and
@@ -373,8 +377,9 @@ int wdg_read_kernel_timing_split(wdg_ctx* ctx, double* ms3, int64_t* launches);
  *   37..39 J_tri h_v / 2, the weights of M^{tri,k} = sum_v (J_tri h_v / 2) M_v
  * (Lemma 1; face Jacobians and normals of Sec. 4.2).  lift: nw x Np_tri x
  * Np_tri, the triangular lift L^{tri,k} = (M^{tri,k})^-1 M^tri (Sec. 4.2),
- * row-major (for N <= 4 the device keeps the lower triangle of
- * (M^{tri,k})^-1 and the product with M^tri is formed here, in FP64).
+ * row-major (the device keeps the lower triangle of (M^{tri,k})^-1 and the
+ * product with M^tri is formed here, in FP64; where the node-lane kernel's
+ * operator exists, L^{tri,k} as stored for it).
  * Either pointer may be NULL. */
 int wdg_get_element_data(const wdg_ctx* ctx, double* geo, double* lift);
 

@@ -419,13 +419,12 @@ int upload_sources(wdg_ctx* ctx) {
 // Whether the wedges of a stage with these flags run on the node-lane kernel:
 // it exists for orders 4 and 5 in FP32, without layer marching and outside
 // the adjoint sweep (which only the level-lane kernel implements).  By default
-// only meshes of a block or two run on it: there a stage is one block's
-// latency either way (24 wedges: 10.1 us against 8.4 level-lane at order 4),
-// and a batch of such problems keeps its search over block shapes.  From 32
-// wedges on the level-lane kernel with a wavefront per equation is the default
-// (us per stage, level-lane against node-lane: order 4 8.8 / 10.4 on 128
-// wedges, 28 / 32 on 18 432, 86 / 106 on 73 728; order 5 11.9 / 14.3,
-// 49 / 53, 156 / 193).
+// the level-lane kernel runs from 32 wedges on (us per stage, level-lane
+// against node-lane: order 4 8.8 / 10.4 on 128 wedges, 28 / 32 on 18 432, 86 /
+// 106 on 73 728; order 5 11.9 / 14.3, 49 / 53, 156 / 193).  Meshes of a block or
+// two keep the node-lane kernel, whose block shapes a batch of them searches:
+// not for speed (24 wedges at order 4 8.6 / 10.2; 512 such meshes in a batch
+// 25 / 34), their results are pinned to it.
 constexpr int64_t kNodeAutoWedges = 32;
 bool node_kernel(const wdg_ctx* ctx, int flags) {
   if (ctx->N < 4 || ctx->bits != 32 || (flags & (wdg::kLayerMarch | wdg::kGrad))) return false;
@@ -449,8 +448,9 @@ int node_lift(wdg_ctx* ctx) {
 
 // Cache policy of the wedge kernel's residual and output state in a stage over
 // state buffers of state_bytes each (two states and the residual) and
-// record_bytes of element records (the tetrahedron, mortar and node-lane kernels
-// always stream what they write).  What fits the 256 MiB Infinity Cache is
+// record_bytes of element records (the other kernels do not follow it: those of
+// the tetrahedra stream what they write, the mortar and node-lane kernels do
+// not).  What fits the 256 MiB Infinity Cache is
 // left to it, the rest streams past the caches: nothing, the residual, or
 // residual and output state.  us per stage, nothing / residual / both streamed:
 // order 3 FP32, 106 496 wedges (215 MiB in all) 51 / - / 63; 122 880 (248 MiB;
@@ -2400,6 +2400,7 @@ struct wdg_batch {
     int N = 0;
     std::vector<int> members;  // problem indices
     bool node = false;         // node-lane kernel (node_kernel), else level-lane
+    std::vector<int> nodes;    // further problems on the node-lane kernel, in the same launch (kBothBlocks)
     int epb = 0, wpe = 2, nwork = 0;
     int2* dWork = nullptr;
     float tuned_us = 0.0f;
@@ -2455,12 +2456,24 @@ void batch_release(wdg_batch* b) {
   b->ready = false;
 }
 
+// Blocks up to which an order's problems on both wedge kernels share a launch:
+// a second launch costs a stage 10 us, the shared kernel runs fewer wavefronts
+// (us per stage, two launches / one, equal numbers of meshes of 24 and 128
+// wedges at order 4: 136 blocks 25.5 / 15.1, 816 29.1 / 26.8, 1088 31.4 / 29.8,
+// 1632 38.1 / 39.2; of 16 and 128 at order 5: 152 28.2 / 17.1, 912 39.3 / 33.9,
+// 1216 45.3 / 45.1, 1824 50.5 / 62.5).
+constexpr size_t kBothBlocks = 1200;
+
 // work list of group g at epb elements per chunk: (problem, chunk), problem-major
 std::vector<int2> batch_work(const wdg_batch* b, const wdg_batch::Group& g, int epb) {
   std::vector<int2> w;
   for (int p : g.members) {
     const int nch = int((b->probs[p]->Kw + epb - 1) / epb);
     for (int c = 0; c < nch; ++c) w.push_back(make_int2(p, c));
+  }
+  for (int p : g.nodes) {
+    const int e = wdg::wedge_both_epb(g.N), nch = int((b->probs[p]->Kw + e - 1) / e);
+    for (int c = 0; c < nch; ++c) w.push_back(make_int2(p, ~c));
   }
   return w;
 }
@@ -2478,11 +2491,10 @@ int batch_upload_records(wdg_batch* b) {
   // a group keeps its kernel for the life of the batch, also where a problem's
   // mesh or kernel was set again
   for (const auto& g : b->groups)
-    for (int p : g.members)
-      if (g.node) {
-        if (const int rc = node_lift(b->probs[p])) return bfail(b, rc, b->probs[p]->err);
-        BHIPCHK(hipStreamSynchronize(b->probs[p]->stream));
-      }
+    for (int p : g.node ? g.members : g.nodes) {
+      if (const int rc = node_lift(b->probs[p])) return bfail(b, rc, b->probs[p]->err);
+      BHIPCHK(hipStreamSynchronize(b->probs[p]->stream));
+    }
   for (size_t i = 0; i < np; ++i) {
     wdg_ctx* ctx = b->probs[i];
     wdg::StageLaunch& A = L[i];
@@ -2527,6 +2539,7 @@ int batch_upload_records(wdg_batch* b) {
 // one stage of group g's problems on stream st with the given kernel shape
 hipError_t launch_group(const wdg_batch* b, const wdg_batch::Group& g, bool node, int epb, int wpe, const int2* work,
                         int nwork, hipStream_t st) {
+  if (!g.nodes.empty()) return wdg::launch_wedge_batch_both(g.N, b->dProbs, work, nwork, st);
   if (node) return wdg::launch_wedge_node_batch(g.N, b->bits, epb, b->dProbs, work, nwork, st);
   return wdg::launch_wedge_batch(g.N, b->bits, b->dProbs, work, nwork, wpe, st);
 }
@@ -2607,6 +2620,16 @@ int wdg_batch_prepare(wdg_batch* b, int autotune) {
             [](const wdg_batch::Group& x, const wdg_batch::Group& y) {
               return x.N != y.N ? x.N > y.N : x.node < y.node;
             });
+  // an order on both kernels: one launch where the blocks are few
+  for (size_t i = 0; i + 1 < b->groups.size(); ++i) {
+    wdg_batch::Group &g = b->groups[i], &h = b->groups[i + 1];
+    if (g.N != h.N) continue;
+    const size_t blocks =
+        batch_work(b, g, wdg::wedge_chunk_elems(g.N, b->bits)).size() + batch_work(b, h, wdg::wedge_both_epb(h.N)).size();
+    if (blocks > kBothBlocks) continue;
+    g.nodes = h.members;
+    b->groups.erase(b->groups.begin() + i + 1);
+  }
   const size_t np = b->probs.size();
   BHIPCHK(hipMalloc(&b->dProbs, np * sizeof(wdg::StageLaunch)));
   BHIPCHK(hipMalloc(&b->dParam, np * sizeof(wdg::BatchParam)));
@@ -2636,7 +2659,8 @@ int wdg_batch_prepare(wdg_batch* b, int autotune) {
     if (g.node) {
       for (int k = 0; k < wdg::kNodeEpbVariants; ++k) cand.push_back({true, wdg::wedge_node_epb(g.N, b->bits, k), 2});
     } else {
-      for (int k = 0; k < 2; ++k)
+      // (one register budget where the launch holds the node-lane kernel too)
+      for (int k = 0; k < (g.nodes.empty() ? 2 : 1); ++k)
         cand.push_back({false, wdg::wedge_chunk_elems(g.N, b->bits), wdg::wedge_waves(g.N, b->bits, k)});
     }
     g.trials.clear();

@@ -172,7 +172,7 @@ hipError_t launch_mortar_stage(int N, int bits, const StageLaunch& a, hipStream_
 hipError_t launch_wedge_stage(int N, int bits, const StageLaunch& a, hipStream_t st);
 hipError_t launch_tet_stage(int N, int bits, const StageLaunch& a, hipStream_t st);
 // N >= 4, FP32: the wedge stage with one lane per triangle node
-// (wedge_node.hip), epb elements per block, one of
+// (wedge_node.hpp), epb elements per block, one of
 // wedge_node_epb(N, bits, 0..kNodeEpbVariants-1) (index 0: the default; 0
 // returned where there is no such kernel).  Not for layer marching or the
 // adjoint sweep.
@@ -204,6 +204,10 @@ int wedge_waves(int N, int bits, int idx);
 // of work; wpe (a wedge_waves value) selects the register budget of the kernel.
 hipError_t launch_wedge_batch(int N, int bits, const StageLaunch* probs, const int2* work, int nwork, int wpe,
                               hipStream_t st);
+// The same for problems of order 4 or 5 in FP32 on both wedge kernels; items of
+// the node-lane kernel hold ~chunk, chunks of wedge_both_epb(N) elements.
+int wedge_both_epb(int N);
+hipError_t launch_wedge_batch_both(int N, const StageLaunch* probs, const int2* work, int nwork, hipStream_t st);
 // Stage s (coefficients a, b) of batch step *counter: writes the
 // stage-dependent fields of every problem's stage record; source amplitudes
 // come from amp[((step * 5 + s) * nprob + problem) * kMaxSources + source],

@@ -9,6 +9,7 @@
 
 #include "device_common.hpp"
 #include "ref_tables.inc"
+#include "wedge_node.hpp"
 
 namespace wdg {
 namespace {
@@ -1195,6 +1196,24 @@ __global__ void __launch_bounds__(256, WPE)
   wedge_stage_chunk_at<N, T, 0>(probs[it.x], it.y);  // the record is wave-uniform: scalar loads
 }
 
+// Problems of one order on both wedge kernels (orders 4 and 5 in FP32) in one
+// launch: a work item with a negative chunk is a chunk ~it.y of the node-lane
+// kernel.  For batches whose blocks are few: a second launch, on a stream of its
+// own or not, costs a stage 10 us (8 meshes of 24 and 8 of 128 wedges at order
+// 4: 25 us per stage in two launches, 15 in one).  The node-lane chunks are small,
+// so that both kernels' LDS leaves three blocks per CU at order 4, two at order 5.
+template <int N>
+constexpr int kBothEpb = N == 4 ? 4 : 3;  // elements per node-lane chunk
+template <int N>
+__global__ void __launch_bounds__(256, N == 4 ? 3 : 2)
+    wedge_batch_both(const StageLaunch* __restrict__ probs, const int2* __restrict__ work, int nwork) {
+  const int w = xcd_chunk(blockIdx.x, gridDim.x);
+  if (w >= nwork) return;
+  const int2 it = work[w];
+  if (it.y >= 0) wedge_stage_chunk_at<N, float, 0>(probs[it.x], it.y);
+  else wedge_node_chunk<N, float, 0, kBothEpb<N>, 256>(probs[it.x], ~it.y);
+}
+
 template <int N, typename T>
 hipError_t launch_wedge_batch_t(const StageLaunch* probs, const int2* work, int nwork, int wpe, hipStream_t st) {
   if (nwork <= 0) return hipSuccess;
@@ -1244,6 +1263,19 @@ int wedge_waves(int N, int bits, int idx) {
   WDG_DISPATCH_N(N, bits, WDG_WAVES)
 #undef WDG_WAVES
   return w - (idx ? 1 : 0);
+}
+
+int wedge_both_epb(int N) { return N == 4 ? kBothEpb<4> : kBothEpb<5>; }
+
+hipError_t launch_wedge_batch_both(int N, const StageLaunch* probs, const int2* work, int nwork, hipStream_t st) {
+  if (nwork <= 0) return hipSuccess;
+  if (N == 4)
+    hipLaunchKernelGGL(wedge_batch_both<4>, dim3(unsigned(nwork)), dim3(256), 0, st, probs, work, nwork);
+  else if (N == 5)
+    hipLaunchKernelGGL(wedge_batch_both<5>, dim3(unsigned(nwork)), dim3(256), 0, st, probs, work, nwork);
+  else
+    return hipErrorInvalidValue;
+  return hipGetLastError();
 }
 
 hipError_t launch_wedge_batch(int N, int bits, const StageLaunch* probs, const int2* work, int nwork, int wpe,

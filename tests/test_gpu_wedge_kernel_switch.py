@@ -78,3 +78,29 @@ def test_batch_keeps_its_kernel_over_a_new_mesh():
     batch.close()
     s.close()
     r.close()
+
+
+@pytest.mark.parametrize("N,nx,layers", [(4, 4, 5), (4, 24, 24), (5, 4, 5), (5, 24, 20)])
+def test_batch_of_both_kernels(N, nx, layers):
+    """Problems below and above 32 wedges in one launch (few blocks) and in two
+    (more than 1200): each ends as it does alone."""
+    batch = wdg.Batch(32, device=0)
+    solvers, alone = [], []
+    for i, (n, lay) in enumerate(((2, 3), (nx, layers), (1, 1))):
+        m = inputs.layered_config(n, lay, 0.3, seed=i)
+        for bucket in (solvers, alone):
+            s = _solver(m, N)
+            s.set_boundary("dirichlet" if i == 0 else "rigid")
+            U = np.zeros((s.K, 4, s.NPmax))
+            U[:, 0] = inputs.gaussian_pulse(s.node_coords(), width=0.3)
+            s.set_fields(U)
+            bucket.append(s)
+        batch.add(solvers[-1], 1e-4 * (i + 1))
+    batch.prepare()
+    batch.step(2)
+    for i, (s, r) in enumerate(zip(solvers, alone)):
+        r.step(2, 1e-4 * (i + 1))
+        assert np.array_equal(s.get_fields(), r.get_fields())
+    batch.close()
+    for s in solvers + alone:
+        s.close()
