@@ -50,11 +50,12 @@ constexpr int stage_waves() {
 // lane = (element, level j).  (One wavefront with all four equations in its
 // registers ran one or two wavefronts per SIMD, and a stage of a small mesh
 // lasted its 3480 VALU instructions: with a wavefront per equation, which does
-// 1000, three to eight run per SIMD.  us per stage before and after: 128 wedges
-// at N = 3 in FP32 11.6 -> 6.8, 262 144 wedges 146 -> 142 (HBM: 688 MB at
-// 4.9 TB/s); N = 4 / 5 in FP32 on 73 728 wedges 117 / 265 -> 86 / 153 (streaming);
-// in FP64 N = 3 on 110 592 160 -> 133, N = 4 on 24 576 264 -> 70.)  LDS holds the staged state as four planes and a
-// second region that first holds the triangular operators, geometry records
+// 1000, two (orders 4 and 5 in FP64) to eight run per SIMD.  us per stage before
+// and after: 128 wedges at N = 3 in FP32 11.6 -> 6.8 (with the host's part of
+// calls of 20 steps 12.1 -> 7.2), 262 144 wedges 146 -> 142 (HBM: 688 MB at
+// 4.9 TB/s); N = 4 / 5 in FP32 on 73 728 wedges 117 / 265 -> 78 / 155; in FP64
+// N = 3 on 110 592 160 -> 134, N = 4 on 24 576 264 -> 69.)  LDS holds the staged
+// state as four planes and a second region that first holds the triangular operators, geometry records
 // and face fluxes, and afterwards the right-hand side, again four planes, on
 // its way to the coalesced update.
 template <int N, typename T>
@@ -827,7 +828,6 @@ __device__ __forceinline__ void wedge_stage_chunk(const StageLaunch& A, int64_t 
       }
     }
   }
-    // ---- phase 1, what needs no neighbour first: the gathers are still in flight
   // pre-lift sums of the wavefront's equation on this level: vertical part
   // W = t_dJ(t_j) (D_t U)(level j)
   T B[NT];
