@@ -155,10 +155,14 @@ __device__ __forceinline__ T dot3(T a, T x, T b, T y, T c, T z) {
   return std::fma(c, z, dot2(a, x, b, y));
 }
 
-// elements whose mass is scaled before it is factored or inverted (kTinyWeight)
+// Factor (a power of two) of an element's mass M^{tri,k} by its first weight, see
+// kTinyWeight: the factored mass takes it back in its entries; what the stored
+// inverse is applied to is multiplied by it, in the few factors that the
+// pre-lift sums and the moments are linear in (a branch around a scaling of the
+// sums themselves cost a stage of 1024 wedges at N = 4 0.3 us of 8.7).
 template <typename T>
-__device__ __forceinline__ bool tiny(T w0) {
-  return sizeof(T) == 4 && w0 < T(kTinyWeight);
+__device__ __forceinline__ T mass_unit(T w0) {
+  return sizeof(T) == 4 && w0 < T(kTinyWeight) ? T(kTinyUp) : T(1);
 }
 
 // 1 / x and 1 / sqrt(x) of positive normal numbers (sums of impedances, whose
@@ -715,6 +719,8 @@ __device__ __forceinline__ void wedge_stage_chunk(const StageLaunch& A, int64_t 
   const T* const elx = elp + 2 * PL;
   const T* const ely = elp + 3 * PL;
   const T* g = sG + (active ? le : 0) * GS;
+  // what the stored inverse is applied to is multiplied by this
+  const T up = C::CHOL ? T(1) : mass_unit(g[37]);
 
   // face fluxes
   if (f != 1) {
@@ -790,12 +796,12 @@ __device__ __forceinline__ void wedge_stage_chunk(const StageLaunch& A, int64_t 
       if (active && j == 0) {
         constexpr int NK = Dim<N>::NPK;
         T w0 = g[37], w1 = g[38], w2 = g[39];
-        const bool small = tiny(w0);
+        const T unit = mass_unit(w0);
+        const bool small = unit != T(1);
         if (__builtin_amdgcn_ballot_w64(small)) {
-          const T up = small ? T(kTinyUp) : T(1);
-          w0 *= up;
-          w1 *= up;
-          w2 *= up;
+          w0 *= unit;
+          w1 *= unit;
+          w2 *= unit;
         }
         T a[4 * VL];
 #pragma unroll
@@ -837,9 +843,9 @@ __device__ __forceinline__ void wedge_stage_chunk(const StageLaunch& A, int64_t 
     lm.row([](auto jj, auto m) { constexpr T v = T(RT::Dt[jj * Nq + m]); return v; }, dtr);
     if (f == 0) {
       const T tl = lm.pick([](auto jj) { constexpr T v = T(0.5 * (1.0 - RT::t[jj])); return v; }), th = T(1) - tl;
-      const T tzJ = g[4];
-      const T txJ = dot2(g[5], tl, g[6], th);
-      const T tyJ = dot2(g[7], tl, g[8], th);
+      const T tzJ = up * g[4];
+      const T txJ = up * dot2(g[5], tl, g[6], th);
+      const T tyJ = up * dot2(g[7], tl, g[8], th);
 #pragma unroll
       for (int i = 0; i < NT; ++i) {
         T dX = 0, dY = 0, dZ = 0;
@@ -853,7 +859,7 @@ __device__ __forceinline__ void wedge_stage_chunk(const StageLaunch& A, int64_t 
       }
     } else {
       const T tl = lm.pick([](auto jj) { constexpr T v = T(0.5 * (1.0 - RT::t[jj])); return v; }), th = T(1) - tl;
-      const T tdJ = f == 1 ? g[4] : dot2(g[2 * f + 1], tl, g[2 * f + 2], th);
+      const T tdJ = up * (f == 1 ? g[4] : dot2(g[2 * f + 1], tl, g[2 * f + 2], th));
 #pragma unroll
       for (int i = 0; i < NT; ++i) {
         T dP = 0;
@@ -893,6 +899,8 @@ __device__ __forceinline__ void wedge_stage_chunk(const StageLaunch& A, int64_t 
       cb = lm.m[0] * wend;
       ct = lm.m[N] * wend;
     }
+    cb *= up;
+    ct *= up;
     if (f != 0) {
       const int c = f == 1 ? 2 : f - 2;  // n_x, n_y, n_z
       cb *= g[13 + c];
@@ -913,7 +921,7 @@ __device__ __forceinline__ void wedge_stage_chunk(const StageLaunch& A, int64_t 
         const auto rb = chunk_rsrc(A.mortB, A.nmort * 2 * Nq * NTP * int64_t(sizeof(T)));
 #pragma unroll
         for (int d = 0; d < 3; ++d) {
-          const T sc = f == 0 ? T(1) : g[22 + 4 * d + f - 2];
+          const T sc = f == 0 ? up : up * g[22 + 4 * d + f - 2];
           const int64_t mo = nbq[d] <= -2 ? int64_t(-2 - nbq[d]) : int64_t(A.nmort);
           const int idx0 = int((mo * 2 * Nq + (f == 0 ? 0 : Nq) + j) * NTP / 4);
 #pragma unroll
@@ -947,11 +955,9 @@ __device__ __forceinline__ void wedge_stage_chunk(const StageLaunch& A, int64_t 
         T Ja = g[20 + 4 * d], Jb = g[21 + 4 * d];
         // a mortar face (-2 - m) takes its flux from the mortar kernel instead
         if (MODE == 2 && nbq[d] <= -2) Ja = Jb = T(0);
-        if (f != 0) {
-          const T nd = g[22 + 4 * d + f - 2];
-          Ja *= nd;
-          Jb *= nd;
-        }
+        const T nd = f == 0 ? up : up * g[22 + 4 * d + f - 2];
+        Ja *= nd;
+        Jb *= nd;
         T fl[Nq];
 #pragma unroll
         for (int q = 0; q < Nq; ++q) fl[q] = fq[d * Nq * Nq + q];
@@ -1010,12 +1016,6 @@ __device__ __forceinline__ void wedge_stage_chunk(const StageLaunch& A, int64_t 
       for (int i = 0; i < NT; ++i) {
         B[i] = R[i];
         R[i] = T(0);
-      }
-      const bool small = tiny(g[37]);
-      if (__builtin_amdgcn_ballot_w64(small)) {
-        const T up = small ? T(kTinyUp) : T(1);
-#pragma unroll
-        for (int i = 0; i < NT; ++i) B[i] *= up;
       }
 #pragma unroll
       for (int c = 0; c < VL; ++c) {
