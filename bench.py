@@ -611,9 +611,9 @@ def main():
     ap.add_argument("--tet-kernel", default="mfma", choices=["mfma", "valu"],
                     help="tetrahedron operator products on the matrix cores (default) or as per-node dot products")
     ap.add_argument("--wedge-kernel", default="auto", choices=["auto", "level", "node"],
-                    help="wedge stage kernel: auto (one lane per triangle node in FP32 at orders 4 and 5, else one "
-                         "lane per GLL level), level (one lane per GLL level) or node (one lane per triangle node at "
-                         "orders 4 and 5 in FP32)")
+                    help="wedge stage kernel: auto (one lane per GLL level; at orders 4 and 5 in FP32 one lane per "
+                         "triangle node below 32 wedges), level (one lane per GLL level) or node (one lane per "
+                         "triangle node at orders 4 and 5 in FP32)")
     ap.add_argument("--cpu-seconds", type=float, default=12.0)
     ap.add_argument("--cpu-sample", type=int, default=1024)
     ap.add_argument("--cpu-workers", type=int, default=0,
@@ -627,7 +627,7 @@ def main():
     ap.add_argument("--batch-steps", type=int, default=300)
     ap.add_argument("--no-legs", action="store_true",
                     help="skip the other forward configurations (cfg2 runs cfg3 with both tetrahedron kernels, "
-                         "cfg5, order 4 and 5 and FP64 cfg2 for 20 steps each)")
+                         "cfg5, order 4 and 5 and FP64 cfg2 for --leg-steps steps each)")
     ap.add_argument("--leg-steps", type=int, default=40)
     ap.add_argument("--no-copy-calibration", action="store_true",
                     help="skip the plain 512 MiB device copy (the measured HBM reference of the roofline)")

@@ -108,7 +108,7 @@ struct StageLaunch {
   void* res;
   const void* geo;   // wedges
   const void* L;     // wedges: (M^{tri,k})^-1, packed (lift_stride)
-  const void* Ln;    // wedges, node-lane kernel: L^{tri,k} column by column (node_lift_stride)
+  const void* Ln;    // wedges on the node-lane kernel: L^{tri,k} column by column (node_lift_stride), else null
   const int* conn;
   const void* geoT;  // tetrahedra
   const int* connT;
@@ -118,7 +118,7 @@ struct StageLaunch {
   const int* mortI;    // mortars: kMortIntStride ints each
   const void* mortG;   // kMortGeoStride FP64 values each
   const void* mortTab; // reference tables of the mortar outputs, type T (see mortar_table_size)
-  const void* mortC;   // per mortar: mort_dev_stride values of type T (coupling matrices)
+  const void* mortC;   // per mortar: mort_dev_stride values of type T (coupling blocks)
   void* mortB;         // per mortar: wedge pre-lift contributions [p, u][Nq][Np_tri padded to 4]
   void* mortF;         // per mortar side: equivalent nodal tetrahedron-face flux [p, u][Np_tri]
   int64_t nmort;
@@ -183,7 +183,9 @@ hipError_t launch_wedge_node_batch(int N, int bits, int epb, const StageLaunch* 
                                    hipStream_t st);
 // Number of values of the mortar reference tables of order N, in this order:
 // Minv1 (Nq x Nq, (M^1D)^-1), ME (3 x Np_tri x Nq: (M^tri)^-1 restricted to the
-// columns of edge e's nodes, [e][i][q]), MTI (Np_tri x Np_tri, (M^tri)^-1).
+// columns of edge e's nodes, [e][i][q]), MTI (Np_tri x Np_tri, (M^tri)^-1), HE
+// (2 x 3 x Np_tri x Nq: those columns times the edge mass weighted by the linear
+// function of the edge's first, then second end, [end][e][i][q]).
 int mortar_table_size(int N);
 // Batches of independent wedge meshes (one launch per order and stage).
 // Per-problem parameters of the stage records written on the device.

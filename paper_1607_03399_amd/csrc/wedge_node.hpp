@@ -2,11 +2,9 @@
 // (Sec. 4.2-4.3: the same stage as wedge_stage.hip, fused volume term,
 // surface fluxes and lifts, L^{tri,k} application and low-storage update).
 //
-// wedge_stage gives each lane a GLL level of an element and keeps the whole
-// triangular slice of the four equations in registers (twice: pre-lift sums
-// and right-hand side), which at N >= 4 pins it to one wavefront per SIMD.
-// Here lane (element, triangle node i) owns the vertical line of node i:
-// its N+1 levels of the four equations (4 (N+1) values), so the kernel runs
+// wedge_stage gives each lane a GLL level of an element, for one of the four
+// equations.  Here lane (element, triangle node i) owns the vertical line of
+// node i: its N+1 levels of the four equations (4 (N+1) values), and runs
 // several wavefronts per SIMD.  The element's state, pre-lift sums and the
 // quadrilateral-face fluxes are shared through LDS; a lane reads the other
 // nodes' values as broadcasts (all lanes of an element read the same address).
